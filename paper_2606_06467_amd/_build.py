@@ -12,8 +12,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libclsa.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ["index_decode.hip", "index_prefill.hip", "topk.hip", "sparse_attn.hip", "project.hip",
-           "kd.hip", "noalloc.hip",
+SOURCES = ["index_decode.hip", "index_prefill.hip", "topk.hip", "sparse_attn.hip", "tile_attn.hip",
+           "project.hip", "kd.hip", "noalloc.hip",
            "api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -32,7 +32,8 @@ COMMON_FLAGS = [
 # layer kernel fits four waves per SIMD (the decode forms, which use no matrix
 # instructions, compile to the same code either way).
 SOURCE_FLAGS = {"kd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-                "sparse_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+                "sparse_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+                "tile_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

@@ -213,6 +213,10 @@ size_t topk_ws_bytes(const Geometry &g) {
     return c.off;
 }
 
+size_t dense_ws_bytes(const Geometry &g) {
+    return align_up(sizeof(float) * clsa::dense_partial_floats(g));
+}
+
 size_t attn_ws_bytes(const Geometry &g, bool dense = false) {
     Carver c{nullptr};
     AttnWs w;
@@ -239,7 +243,7 @@ size_t clsa_workspace_bytes(const clsa_shape *shape, int32_t op, int32_t n_layer
             return attn_ws_bytes(g);
         case CLSA_OP_DENSE:
             if (check_shape(shape, kAttn | kDense, &g) != CLSA_OK) return 0;
-            return attn_ws_bytes(g, true);
+            return dense_ws_bytes(g);
         case CLSA_OP_KD_TARGET:
             if (check_shape(shape, kAttn, &g) != CLSA_OK || n_layers < 1 ||
                 !clsa::kd_target_supported(g, n_layers))
@@ -512,11 +516,11 @@ clsa_status clsa_dense_attn(const clsa_shape *shape, const void *q, const void *
     CLSA_TRY(check_common(shape, page_table, q_pos, true, true));
     const size_t need = attn_ws_bytes(g, true);
     if (need && (!ws || ws_bytes < need || !aligned(ws, kAlign))) return CLSA_ERR_WORKSPACE;
-    Carver c{static_cast<char *>(ws)};
-    AttnWs w;
-    carve_attn(g, c, w, true);
+    // a workspace past the least one is used for a finer key split
+    const bool usable = ws && aligned(ws, kAlign);
     return from_hip(clsa::launch_dense_attn(g, q, k_cache, v_cache, page_table, seq_lens, q_pos,
-                                            out, lse, w.partials,
+                                            out, lse, usable ? static_cast<float *>(ws) : nullptr,
+                                            usable ? ws_bytes / sizeof(float) : 0,
                                             static_cast<hipStream_t>(stream)));
 }
 
@@ -597,6 +601,7 @@ clsa_status clsa_get_device_error(uint32_t *bits) {
     CLSA_TRY(from_hip(clsa::take_device_error_index_prefill(&v)));
     CLSA_TRY(from_hip(clsa::take_device_error_topk(&v)));
     CLSA_TRY(from_hip(clsa::take_device_error_sparse_attn(&v)));
+    CLSA_TRY(from_hip(clsa::take_device_error_tile_attn(&v)));
     CLSA_TRY(from_hip(clsa::take_device_error_kd(&v)));
     *bits = v;
     return CLSA_OK;

@@ -159,7 +159,30 @@ hipError_t launch_sparse_attn(const Geometry &g, const void *q, const void *k_ca
 hipError_t launch_dense_attn(const Geometry &g, const void *q, const void *k_cache,
                              const void *v_cache, const int32_t *page_table,
                              const int32_t *seq_lens, const int32_t *q_pos, void *out, float *lse,
-                             float *partials, hipStream_t stream);
+                             float *partials, size_t partial_floats, hipStream_t stream);
+// Partial buffer floats of dense attention: attn_partial_floats(g, true) are
+// enough; with dense_partial_floats(g), many rows over few row blocks split their
+// keys over enough workgroups to fill the chip.
+size_t dense_partial_floats(const Geometry &g);
+
+// ---- tile_attn.hip ----
+// Query rows per sequence from which dense attention runs over key tiles shared
+// by a block of rows (16 rows, half of a block's 32, against one gather per row:
+// 2000 keys 15.1 us each way, 32768 keys 41 against 112, 8 x 4096 keys 43 against
+// 101; from 24 rows on faster everywhere measured), and the workgroups aimed at
+// (two per CU, by splitting the key range).
+constexpr int kTileAttnMinRows = 16;
+constexpr int kTileAttnWorkgroups = 512;
+bool tile_attn_dense(const Geometry &g);
+// Key ranges per row (at most max_splits) and keys per range.
+void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span);
+// mask: null, or the selection mask.  Partials as in sparse_attn.hip when splits > 1.
+hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cache,
+                            const void *v_cache, const int32_t *page_table,
+                            const int32_t *seq_lens, const int32_t *q_pos, const uint32_t *mask,
+                            int splits, int span, void *out, float *lse, float *part_o,
+                            float *part_ml, hipStream_t stream);
+hipError_t take_device_error_tile_attn(uint32_t *bits);
 
 // ---- project.hip ----
 // d_model values the projection kernels support (multiples of 512 up to 8192).

@@ -792,6 +792,32 @@ size_t attn_partial_floats(const Geometry &g, bool dense) {
     return (size_t)g.rows * g.q_heads * splits * (kHeadDim + 2);
 }
 
+size_t dense_partial_floats(const Geometry &g) {
+    const size_t least = attn_partial_floats(g, true);
+    if (!tile_attn_dense(g)) return least;
+    int splits, span;
+    tile_attn_plan(g, kMaxSplits, splits, span);
+    if (splits == 1) return least;
+    const size_t best = (size_t)g.rows * g.q_heads * splits * (kHeadDim + 2);
+    return best > least ? best : least;
+}
+
+// Combines the splits' partials; units: (row, query head) pairs.
+template <bool DENSE>
+static hipError_t launch_merge(const AttnArgs &a, int units, hipStream_t stream) {
+    const dim3 mgrid(units), mblock(256), wblock(64);
+    // up to 4 splits: one wave per (row, query head) (32K step layers -1.7 us,
+    // 32-sequence ragged batch -6.5 us); 8 splits measured faster on the
+    // 256-thread form (128K layers 158.1 against 162.5 us)
+    if (a.splits <= 4) attn_merge_wave_kernel<4, DENSE><<<mgrid, wblock, 0, stream>>>(a);
+    else if (a.splits <= 8) attn_merge_kernel<1, DENSE><<<mgrid, mblock, 0, stream>>>(a);
+    else if (a.splits <= 16) attn_merge_kernel<2, DENSE><<<mgrid, mblock, 0, stream>>>(a);
+    else if (a.splits <= 32) attn_merge_kernel<4, DENSE><<<mgrid, mblock, 0, stream>>>(a);
+    else if (a.splits <= 64) attn_merge_kernel<8, DENSE><<<mgrid, mblock, 0, stream>>>(a);
+    else attn_merge_kernel<16, DENSE><<<mgrid, mblock, 0, stream>>>(a);
+    return hipGetLastError();
+}
+
 template <int G, bool DENSE>
 static hipError_t launch_attn_g(const AttnArgs &a, bool paged, dim3 grid, int units,
                                 hipStream_t stream, hipEvent_t split_done) {
@@ -807,17 +833,7 @@ static hipError_t launch_attn_g(const AttnArgs &a, bool paged, dim3 grid, int un
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && split_done) e = hipEventRecord(split_done, stream);
     if (e != hipSuccess || a.splits == 1 || a.tickets) return e;
-    const dim3 mgrid(units), mblock(256), wblock(64);
-    // up to 4 splits: one wave per (row, query head) (32K step layers -1.7 us,
-    // 32-sequence ragged batch -6.5 us); 8 splits measured faster on the
-    // 256-thread form (128K layers 158.1 against 162.5 us)
-    if (a.splits <= 4) attn_merge_wave_kernel<4, DENSE><<<mgrid, wblock, 0, stream>>>(a);
-    else if (a.splits <= 8) attn_merge_kernel<1, DENSE><<<mgrid, mblock, 0, stream>>>(a);
-    else if (a.splits <= 16) attn_merge_kernel<2, DENSE><<<mgrid, mblock, 0, stream>>>(a);
-    else if (a.splits <= 32) attn_merge_kernel<4, DENSE><<<mgrid, mblock, 0, stream>>>(a);
-    else if (a.splits <= 64) attn_merge_kernel<8, DENSE><<<mgrid, mblock, 0, stream>>>(a);
-    else attn_merge_kernel<16, DENSE><<<mgrid, mblock, 0, stream>>>(a);
-    return hipGetLastError();
+    return launch_merge<DENSE>(a, units, stream);
 }
 
 template <bool DENSE>
@@ -885,14 +901,32 @@ hipError_t launch_sparse_attn(const Geometry &g, const void *q, const void *k_ca
 hipError_t launch_dense_attn(const Geometry &g, const void *q, const void *k_cache,
                              const void *v_cache, const int32_t *page_table,
                              const int32_t *seq_lens, const int32_t *q_pos, void *out, float *lse,
-                             float *partials, hipStream_t stream) {
+                             float *partials, size_t partial_floats, hipStream_t stream) {
     AttnArgs a = attn_args(g, q, k_cache, v_cache, page_table, out, lse, partials, true);
     a.seq_lens = seq_lens;
     a.q_pos = q_pos;
     if (g.rows == 0) return hipSuccess;
+    const int units = g.rows * g.q_heads;
+    if (tile_attn_dense(g)) {
+        int splits, span;
+        tile_attn_plan(g, kMaxSplits, splits, span);
+        const size_t slots = (size_t)g.rows * g.q_heads * splits;
+        // a partial buffer of the least size does not hold the split that fills
+        // the chip; the per-row kernel is then the faster one (16 rows of 32768
+        // keys: 112-117 us per row, 142 in tiles over two ranges, 42 over 64)
+        if (splits == 1 || partial_floats >= slots * (kHeadDim + 2)) {
+            a.splits = splits;
+            a.chunks_per_split = span / 64;
+            a.part_o = partials;
+            a.part_ml = partials + slots * kHeadDim;
+            const hipError_t e =
+                launch_tile_attn(g, q, k_cache, v_cache, page_table, seq_lens, q_pos, nullptr,
+                                 splits, span, out, lse, a.part_o, a.part_ml, stream);
+            return e != hipSuccess || splits == 1 ? e : launch_merge<true>(a, units, stream);
+        }
+    }
     const size_t blocks = (size_t)g.rows * g.kv_heads * a.splits;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-    const int units = g.rows * g.q_heads;
     return launch_attn<true>(g, a, g.page_shift >= 0, dim3((unsigned)blocks), units, stream,
                              nullptr);
 }

@@ -1,0 +1,83 @@
+"""GPU parity of attention over key tiles shared by a block of query rows
+(dense attention of many rows per sequence) against the fp64 oracle: the edges
+of its 32-row blocks and 64-key tiles, every GQA group, key ranges merged
+afterwards, rows without keys, and values that are not finite outside a row's
+keys.  Tolerances as for every attention output (tests/gpu_util.py)."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2606_06467_amd import inputs
+from tests import gpu_util as U
+from tests.test_gpu_dense import _case, _full_sets
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nq,n,ps", [(16, 63, 0), (31, 64, 16), (32, 65, 0), (33, 127, 64),
+                                     (65, 129, 0), (130, 1000, 64)])
+@pytest.mark.parametrize("qh,kvh", [(4, 4), (4, 2), (32, 8), (10, 2), (16, 2)])
+def test_tile_edges(nq, n, ps, qh, kvh):
+    """Causal rows that end with their sequence; the second sequence is shorter
+    than the block of rows (its first rows see nothing), the third is empty."""
+    w = inputs.small_workload(batch=3, lens=(n, nq // 2, 0), n_q=nq, causal=True,
+                              q_pos0=(n - nq, nq // 2 - nq, -nq), q_heads=qh, kv_heads=kvh,
+                              page_size=ps, n_layers=1, wid=81)
+    _case(w, f"tiles {nq} rows {n} keys Hq={qh} Hkv={kvh} page={ps}")
+
+
+@pytest.mark.parametrize("nq,n", [(16, 3000), (40, 5000)])
+def test_not_causal_split_by_key_range(nq, n):
+    """Few row blocks: the key range is split and merged; every row sees every key."""
+    w = inputs.small_workload(batch=2, lens=(n, n // 3), n_q=nq, n_layers=1, wid=82)
+    _case(w, f"tiles {nq} rows {n} keys, split")
+
+
+def test_large_logits():
+    """Logits of hundreds: the running maximum moves far, in both directions."""
+    w = inputs.small_workload(batch=1, lens=(400,), n_q=40, causal=True, q_pos0=(360,),
+                              n_layers=1, wid=83)
+    x = inputs.make_inputs(w, layers=[0])
+    k = inputs.f32_from_bf16_bits(x["k_cache"])
+    k *= np.linspace(-30, 30, 400)[None, :, None, None]
+    x["k_cache"] = inputs.bf16_bits_from_f32(k)
+    _run_and_compare(w, x)
+
+
+def _run_and_compare(w, x, mask_rows=None):
+    import torch
+    from paper_2606_06467_amd import binding as B
+    d = U.to_dev(x)
+    q = B.bf16_from_bits(x["q_layers"][0])
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full(q.shape[:-1], float("nan"), device="cuda")
+    sh = U.shape_of(w)
+    B.clsa_dense_attn(sh, q, d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"],
+                      d["q_pos"], out, lse, B.workspace(sh, B.CLSA_OP_DENSE))
+    torch.cuda.synchronize()
+    osh, idx, n = _full_sets(w, x["seq_lens"], x["q_pos"])
+    ref_o, ref_l = orc.sparse_attn(osh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, n,
+                                   x["page_table"])
+    o = B.bits_from_bf16(out)
+    ls = lse.cpu().numpy().astype(np.float64)
+    U.compare_attn(o, ls, ref_o, ref_l, mask_rows=mask_rows)
+    return inputs.f32_from_bf16_bits(o), ls
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("which", ["k_cache", "v_cache"])
+def test_values_not_finite_stay_with_the_rows_that_see_them(which, bad):
+    """A token whose key or value is not finite changes no row before it."""
+    w = inputs.small_workload(batch=1, lens=(300,), n_q=70, causal=True, q_pos0=(230,),
+                              n_layers=1, wid=84)
+    x = inputs.make_inputs(w, layers=[0])
+    x["k_cache"] = x["k_cache"].copy()
+    x["v_cache"] = x["v_cache"].copy()
+    x[which][0, 250, :, 5] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
+    before = np.zeros((1, 70), bool)
+    before[0, :20] = True  # positions 230 .. 249
+    o, ls = _run_and_compare(w, x, mask_rows=before)
+    if which == "v_cache":  # the others carry it, in that dimension alone
+        assert not np.isfinite(o[0, 20:, :, 5]).any()
+        assert np.isfinite(np.delete(o[0, 20:], 5, axis=-1)).all()
+        assert np.isfinite(ls).all()
