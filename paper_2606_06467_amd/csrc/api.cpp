@@ -375,6 +375,10 @@ clsa_status decode_step_impl(const clsa_shape *shape, const void *q_idx, int64_t
     // sampled pass sets each row's candidate threshold and a second pass
     // emits the candidates (see topk.hip).
     const bool two_pass = clsa::topk_uses_two_pass(g);
+    // Chunked prefill over few enough keys attends in key tiles with a selection
+    // mask; the mask takes the place of the split partials, which it needs none of.
+    const bool masked = n_layers > 0 && clsa::tile_attn_masked(g, clsa::attn_partial_floats(g));
+    uint32_t *mask = reinterpret_cast<uint32_t *>(w.partials);
     const size_t q_stride = (size_t)g.rows * g.q_heads * 128;  // bf16 elements per layer
     const size_t lse_stride = (size_t)g.rows * g.q_heads;
     const size_t set_stride = (size_t)g.rows * g.top_k;         // index entries per set
@@ -418,6 +422,8 @@ clsa_status decode_step_impl(const clsa_shape *shape, const void *q_idx, int64_t
         }
         if (first && hook && hipEventRecord(t_hook.ev[2], st) != hipSuccess) return CLSA_ERR_HIP;
         const int l_end = n_layers < (s + 1) * group ? n_layers : (s + 1) * group;
+        if (masked)
+            CLSA_TRY(from_hip(clsa::launch_attn_mask(g, is, ns, seq_lens, mask, st)));
         for (int l = s * group; l < l_end; ++l) {
             const uint16_t *ql = static_cast<const uint16_t *>(q_layers) + l * q_stride;
             uint16_t *ol = static_cast<uint16_t *>(out_layers) + l * q_stride;
@@ -425,6 +431,13 @@ clsa_status decode_step_impl(const clsa_shape *shape, const void *q_idx, int64_t
             const bool mark = hook && l < t_hook.layers;
             if (mark && hipEventRecord(t_hook.ev[4 + 2 * l], st) != hipSuccess)
                 return CLSA_ERR_HIP;
+            if (masked) {
+                CLSA_TRY(from_hip(clsa::launch_masked_attn(g, ql, k_cache, v_cache, page_table,
+                                                           seq_lens, q_pos, mask, ol, lsel, st)));
+                if (mark && hipEventRecord(t_hook.ev[5 + 2 * l], st) != hipSuccess)
+                    return CLSA_ERR_HIP;
+                continue;
+            }
             CLSA_TRY(from_hip(clsa::launch_sparse_attn(g, ql, k_cache, v_cache, page_table, is,
                                                        ns, ol, lsel, w.partials, w.tickets, st,
                                                        mark ? t_hook.ev[5 + 2 * l] : nullptr)));

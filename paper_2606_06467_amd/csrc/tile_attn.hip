@@ -3,12 +3,11 @@
 // prefill whose rows select a large part of their keys, the sparse attention
 // of Eq. 4 as dense tiles with a selection mask.
 //
-// Work unit: one workgroup = 32 * RB query rows of one sequence x the G query
-// heads of one KV head, one wave per (head, 32 rows).  The KV head's keys and
-// values pass through LDS 64 at a time, double-buffered (the next tile's
-// global loads are in flight during the current products, one barrier per
-// tile), and each staged tile serves every wave, instead of being gathered
-// again by every row as in the per-row kernel.
+// Work unit: one workgroup of 8 waves, one wave per (32 query rows, query head)
+// of one KV head, the heads of a row block next to each other.  The KV head's
+// keys and values pass through LDS 64 at a time, double-buffered, one barrier
+// per tile, and each staged tile serves all eight waves, instead of being
+// gathered again by every row as in the per-row kernel.
 //
 // Per 64-key tile and wave (v_mfma_f32_32x32x16_bf16; lane l supplies A row /
 // B column (l & 31) for contraction indices 8 * (l >> 5) .. + 8, and receives
@@ -22,11 +21,19 @@
 //     slot (hi, j) of a 16-key step stands for key 4 hi + (j & 3) + 8 (j >> 2)),
 //     so they never leave their registers; A = V^T by ds_read_b64_tr_b16, the
 //     transposing LDS read, from the row-major value tile.
-// Measured, one layer of 8192 causal rows, 20 query and 4 KV heads: 0.56 ms
-// (3.4e11 FLOP, 610 TFLOP/s) against 2.7-2.8 ms with every row gathering its
-// own keys (127 TFLOP/s, held by the L2).
-// The running maximum moves lazily: only when a logit exceeds it by 2^kLazy
+// The running maximum moves lazily: only when a logit exceeds it by 2^kTaLazy
 // (a wave-uniform branch), so that the steady state rescales nothing.
+// What bounds it: a wave alternates matrix products and the exponentials that
+// depend on them, at two waves per SIMD (the accumulators, queries and two
+// tiles' logits fill 256 registers).  The loop is therefore pipelined by one
+// tile: the products of tile u + 1 stand beside the exponentials of tile u, and
+// the weighted values of tile u beside the maximum of tile u + 1.
+// Measured, one layer of 8192 causal rows, 20 query and 4 KV heads (3.4e11
+// FLOP): every row gathering its own keys 2.7-2.8 ms (127 TFLOP/s); these tiles
+// with the steps of a tile one after another, one wave per head, 0.56; pipelined
+// with four waves per workgroup 0.46, with eight 0.41, and the key registers
+// stored between the two halves (no spill) 0.397 ms: 860 TFLOP/s, 71% of what
+// the library GEMM reaches on 8192^3 (1216).
 #include "clsa_internal.h"
 #include "device_common.h"
 
@@ -47,14 +54,14 @@ constexpr float kTaLn2 = 0.6931471805599453f;
 struct TileAttnArgs {
     const uint16_t *q, *k, *v;
     const int32_t *page_table, *seq_lens, *q_pos;
-    const uint64_t *mask;  // [batch * mask_blocks, mask_pitch] lane masks, or null (dense)
+    const uint32_t *mask;  // [rows, mask_pitch] words of 32 keys, or null (dense)
     uint16_t *out;
     float *lse;            // may be null
     float *part_o, *part_ml;
     int batch, n_q, max_len, page_shift, max_pages, causal, kv_heads, q_heads;
-    int row_blocks;        // blocks of 32 * RB rows per sequence
+    int group, row_blocks; // query heads per KV head, blocks of NW (32 rows, head) pairs per sequence
     int splits, span;      // key ranges per row, keys per range (a multiple of kTaKeys)
-    int mask_blocks, mask_pitch;  // 32-row blocks per sequence, 64-bit masks per block
+    int mask_pitch;        // words per row (two per tile)
     float scale_log2;
 };
 
@@ -79,13 +86,6 @@ __device__ __forceinline__ int wave_min_i(int x) {
     return x;
 }
 
-// Position of key j of a 32-key block among the block's 32 mask words: word
-// 2 r + hi belongs to the key that lanes of half hi hold in C register r, so
-// that a 64-bit word is the lane mask of one register.
-__host__ __device__ constexpr int mask_word(int j) {
-    return 2 * (4 * (j >> 3) + (j & 3)) + ((j >> 2) & 1);
-}
-
 // The wave's queries one by one, one key at a time (2 dimensions per lane),
 // every value exactly as selected: taken only when a tile product met an
 // infinity or a NaN, which a weight of zero does not remove from a product, so
@@ -103,9 +103,8 @@ __device__ __forceinline__ void tile_attn_rows(const TileAttnArgs &a, int b, int
         float m = -INFINITY, l = 0.0f, ox = 0.0f, oy = 0.0f;
         for (int j = split * a.span; j < j_end; ++j) {
             if (MASK) {
-                const uint32_t *w = reinterpret_cast<const uint32_t *>(
-                    a.mask + ((size_t)b * a.mask_blocks + (t0 >> 5)) * a.mask_pitch);
-                if (!((w[(j & ~31) + mask_word(j & 31)] >> i) & 1u)) continue;  // uniform
+                if (!((a.mask[(size_t)row * a.mask_pitch + (j >> 5)] >> (j & 31)) & 1u))
+                    continue;  // uniform
             }
             const size_t off = token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b, j,
                                             a.kv_heads * kTaDim) + (size_t)g * kTaDim + 2 * lane;
@@ -134,11 +133,10 @@ __device__ __forceinline__ void tile_attn_rows(const TileAttnArgs &a, int b, int
     }
 }
 
-template <int G, int RB, bool PAGED, bool MASK>
-__global__ __launch_bounds__(64 * G * RB, 2) void tile_attn_kernel(TileAttnArgs a) {
-    constexpr int NW = G * RB, NT = 64 * NW;
-    constexpr int PIECES = kTaKeys * kTaDim / 8;          // 16-byte pieces of a tile
-    constexpr int PER = (PIECES + NT - 1) / NT;           // per thread
+template <int NW, bool PAGED, bool MASK>
+__global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
+    constexpr int NT = 64 * NW;
+    constexpr int PER = kTaKeys * kTaDim / 8 / NT;  // 16-byte pieces of a tile per thread
     __shared__ __align__(16) uint16_t s_k[2][kTaKeys][kTaKPitch];
     __shared__ __align__(16) uint16_t s_v[2][kTaKeys][kTaVPitch];
     __shared__ int s_lim[NW];
@@ -151,8 +149,9 @@ __global__ __launch_bounds__(64 * G * RB, 2) void tile_attn_kernel(TileAttnArgs 
     const int split = x / a.row_blocks;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, hi = lane >> 5;
-    const int h = g * G + wave % G;
-    const int t0 = rblk * 32 * RB + (wave / G) * 32;       // the wave's first row
+    const int pair = rblk * NW + wave;                     // (32-row block, head of the group)
+    const int h = g * a.group + pair % a.group;
+    const int t0 = (pair / a.group) * 32;                  // the wave's first row
     const int t = t0 + col;                                // this lane's query
     const int len = clamp_len(a.seq_lens[b], a.max_len);
     const int row = b * a.n_q + min(t, a.n_q - 1);
@@ -182,12 +181,13 @@ __global__ __launch_bounds__(64 * G * RB, 2) void tile_attn_kernel(TileAttnArgs 
         for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
     float m = -INFINITY, l = 0.0f;
 
-    u32x4 kr[PER], vr[PER];
-    auto fetch = [&](int j0) {
+    // staging: thread -> 16-byte piece (tid & 15) of key rows (tid >> 4) + i * NT / 16;
+    // keys past len are clamped (and masked)
+    const int srow = tid >> 4, spc = (tid & 15) * 8;
+    auto fetch = [&](const uint16_t *base, int j0, u32x4 (&v)[PER]) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int pc = tid + i * NT;
-            const int j = min(j0 + min(pc >> 4, kTaKeys - 1), len - 1);  // keys past len: masked
+            const int j = min(j0 + srow + i * (NT / 16), len - 1);
             size_t tok;
             if (PAGED) {
                 const int page = a.page_table[(size_t)b * a.max_pages + (j >> a.page_shift)];
@@ -195,105 +195,148 @@ __global__ __launch_bounds__(64 * G * RB, 2) void tile_attn_kernel(TileAttnArgs 
             } else {
                 tok = (size_t)b * a.max_len + j;
             }
-            const size_t off = (tok * a.kv_heads + g) * kTaDim + (pc & 15) * 8;
-            kr[i] = *reinterpret_cast<const u32x4 *>(a.k + off);
-            vr[i] = *reinterpret_cast<const u32x4 *>(a.v + off);
+            v[i] = *reinterpret_cast<const u32x4 *>(base + (tok * a.kv_heads + g) * kTaDim + spc);
         }
     };
-    auto stage = [&](int buf) {
+    auto stage_k = [&](int buf, const u32x4 (&v)[PER]) {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int pc = tid + i * NT;
-            if (PIECES % NT == 0 || pc < PIECES) {
-                *reinterpret_cast<u32x4 *>(&s_k[buf][pc >> 4][(pc & 15) * 8]) = kr[i];
-                *reinterpret_cast<u32x4 *>(&s_v[buf][pc >> 4][(pc & 15) * 8]) = vr[i];
-            }
-        }
+        for (int i = 0; i < PER; ++i)
+            *reinterpret_cast<u32x4 *>(&s_k[buf][srow + i * (NT / 16)][spc]) = v[i];
     };
-    if (tiles > 0) {
-        fetch(j_begin);
-        stage(0);
-    }
-    __syncthreads();
+    auto stage_v = [&](int buf, const u32x4 (&v)[PER]) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            *reinterpret_cast<u32x4 *>(&s_v[buf][srow + i * (NT / 16)][spc]) = v[i];
+    };
     // transposing V reads: lane i of a 16-lane group q reads row 4 hi + (i >> 2),
     // columns 16 (q & 1) + 4 (i & 3) .. + 4, and receives column i of the 4 x 16 block
     const int vrow = 4 * hi + ((lane & 15) >> 2);
     const int vcol = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    const uint64_t *mrow = MASK ? a.mask + ((size_t)b * a.mask_blocks + min(t0 >> 5, a.mask_blocks - 1)) *
-                                               a.mask_pitch
-                                : nullptr;
-    for (int u = 0; u < tiles; ++u) {
-        const int j0 = j_begin + u * kTaKeys, buf = u & 1;
-        if (u + 1 < tiles) fetch(j0 + kTaKeys);
-        if (j0 < nmax) {  // uniform per wave
-            f32x16 s[2];
+    // the row's selection words of a tile
+    const uint2 *mrow = reinterpret_cast<const uint2 *>(MASK ? a.mask + (size_t)row * a.mask_pitch
+                                                             : nullptr);
+    auto words = [&](int j0) {
+        return mrow[min(j0 / kTaKeys, a.mask_pitch / 2 - 1)];
+    };
+    auto logits = [&](int buf, f32x16 (&s)[2]) {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[kt][r] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[kt][r] = 0.0f;
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    const bf16x8 ka = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u32x4 *>(&s_k[buf][32 * kt + col][16 * ks + 8 * hi]));
-                    s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[ks], s[kt], 0, 0, 0);
-                }
+                const bf16x8 ka = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const u32x4 *>(&s_k[buf][32 * kt + col][16 * ks + 8 * hi]));
+                s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[ks], s[kt], 0, 0, 0);
             }
-            if (MASK) {
-#pragma unroll
-                for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        s[kt][r] = __builtin_amdgcn_inverse_ballot_w64(mrow[(j0 >> 1) + 16 * kt + r])
-                                       ? s[kt][r]
-                                       : -INFINITY;
-            } else if (j0 + kTaKeys > nmin) {
-#pragma unroll
-                for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        s[kt][r] = j0 + 32 * kt + 8 * (r >> 2) + 4 * hi + (r & 3) < n ? s[kt][r]
-                                                                                      : -INFINITY;
-            }
-            float mx = fmaxf(s[0][0], s[1][0]);
-#pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(s[0][r], s[1][r]));
-            mx = pair_max(mx * a.scale_log2);
-            if (__builtin_amdgcn_ballot_w64(mx > m + kTaLazy)) {
-                const float nm = fmaxf(m, mx);
-                const float f = nm == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - nm);
-                m = nm;
-                l *= f;
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[d][r] *= f;
-            }
-            const float base = m == -INFINITY ? 0.0f : m;
-            bf16x8 pb[4];
+    };
+    auto drop = [&](int j0, uint2 w, f32x16 (&s)[2]) {  // keys outside a row's set
+        if (MASK && __builtin_amdgcn_ballot_w64((w.x & w.y) != ~0u)) {
+            w.x >>= 4 * hi;
+            w.y >>= 4 * hi;
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(s[kt][r], a.scale_log2, -base));
-                    l += p;
-                    pb[2 * kt + (r >> 3)][r & 7] = (__bf16)p;
+                for (int r = 0; r < 16; ++r) {  // v_bfe_i32 (0 or -1) and v_bfi_b32
+                    const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)(kt ? w.y : w.x),
+                                                                        8 * (r >> 2) + (r & 3), 1);
+                    s[kt][r] = __uint_as_float((__float_as_uint(s[kt][r]) & on) | (0xff800000u & ~on));
                 }
+        } else if (!MASK && j0 + kTaKeys > nmin) {
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
+            for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    typedef __attribute__((address_space(3))) s16x4 lds4;
-                    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (lds4 *)&s_v[buf][16 * kb + vrow][32 * d + vcol]);
-                    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (lds4 *)&s_v[buf][16 * kb + 8 + vrow][32 * d + vcol]);
-                    const bf16x8 va = __builtin_bit_cast(
-                        bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-                    o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[kb], o[d], 0, 0, 0);
-                }
+                for (int r = 0; r < 16; ++r)
+                    s[kt][r] = j0 + 32 * kt + 8 * (r >> 2) + 4 * hi + (r & 3) < n ? s[kt][r]
+                                                                                  : -INFINITY;
         }
-        if (u + 1 < tiles) stage(buf ^ 1);
+    };
+    auto largest = [&](const f32x16 (&s)[2]) {
+        float mx = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(s[0][r], s[1][r]));
+        return pair_max(mx * a.scale_log2);
+    };
+    auto rebase = [&](float mx) {
+        if (__builtin_amdgcn_ballot_w64(mx > m + kTaLazy)) {
+            const float nm = fmaxf(m, mx);
+            const float f = nm == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - nm);
+            m = nm;
+            l *= f;
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[d][r] *= f;
+        }
+    };
+    auto weights = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4]) {
+        const float base = m == -INFINITY ? 0.0f : m;
+        float sum[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[kt][r], a.scale_log2, -base));
+                sum[kt] += p;
+                pb[2 * kt + (r >> 3)][r & 7] = (__bf16)p;
+            }
+        l += sum[0] + sum[1];
+    };
+    auto weighted = [&](int buf, const bf16x8 (&pb)[4]) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                typedef __attribute__((address_space(3))) s16x4 lds4;
+                const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds4 *)&s_v[buf][16 * kb + vrow][32 * d + vcol]);
+                const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds4 *)&s_v[buf][16 * kb + 8 + vrow][32 * d + vcol]);
+                const bf16x8 va = __builtin_bit_cast(
+                    bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[kb], o[d], 0, 0, 0);
+            }
+    };
+    u32x4 kr[PER], vr[PER];
+    if (tiles > 0) {  // uniform over the workgroup
+        fetch(a.k, j_begin, kr);
+        fetch(a.v, j_begin, vr);
+        stage_k(0, kr);
+        stage_v(0, vr);
+        fetch(a.k, j_begin + kTaKeys, kr);
+        stage_k(1, kr);
         __syncthreads();
+        f32x16 s[2];
+        logits(0, s);
+        drop(j_begin, MASK ? words(j_begin) : make_uint2(0u, 0u), s);
+        rebase(largest(s));
+        for (int u = 0; u + 1 < tiles; ++u) {
+            const int j0 = j_begin + u * kTaKeys, buf = u & 1;
+            fetch(a.k, j0 + 2 * kTaKeys, kr);
+            fetch(a.v, j0 + kTaKeys, vr);
+            const uint2 w = MASK ? words(j0 + kTaKeys) : make_uint2(0u, 0u);
+            f32x16 sn[2];
+            bf16x8 pb[4];
+            __builtin_amdgcn_sched_barrier(0);
+            logits(buf ^ 1, sn);
+            weights(s, pb);
+            __builtin_amdgcn_sched_barrier(0);
+            stage_k(buf, kr);
+            drop(j0 + kTaKeys, w, sn);
+            weighted(buf, pb);
+            const float mx = largest(sn);
+            __builtin_amdgcn_sched_barrier(0);
+            stage_v(buf ^ 1, vr);
+            rebase(mx);
+            __syncthreads();
+            s[0] = sn[0];
+            s[1] = sn[1];
+        }
+        bf16x8 pb[4];
+        weights(s, pb);
+        weighted((tiles - 1) & 1, pb);
     }
     if (t0 >= a.n_q) return;
     l = pair_sum(l);
@@ -336,13 +379,56 @@ __global__ __launch_bounds__(64 * G * RB, 2) void tile_attn_kernel(TileAttnArgs 
     if (a.lse && hi == 0) a.lse[rh] = (m + log2f(l)) * kTaLn2;
 }
 
-// Rows per workgroup: 32 per head and wave, four waves or one per head.
-static int tile_rows(int group) { return group == 1 ? 128 : group == 2 ? 64 : 32; }
+struct MaskArgs {
+    const int32_t *idx, *n_sel, *seq_lens;  // [rows, top_k], [rows], [batch]
+    uint32_t *mask;                         // [rows, pitch]
+    int n_q, max_len, top_k, pitch;
+};
+
+// The selection mask of tile_attn_kernel from the (ascending) index lists: one
+// bit per key, a workgroup per row.  Each thread takes a run of consecutive
+// entries and ORs its finished words into LDS, so that dense lists cost few LDS
+// operations; a row longer than kMaskKeys takes several passes.
+constexpr int kMaskKeys = 65536, kMaskThreads = 256;
+__global__ __launch_bounds__(kMaskThreads) void attn_mask_kernel(MaskArgs a) {
+    __shared__ uint32_t w[kMaskKeys / 32];
+    const size_t row = blockIdx.x;
+    const int b = (int)row / a.n_q, tid = threadIdx.x;
+    const int len = clamp_len(a.seq_lens[b], a.max_len);
+    const int end = div_up(len, kTaKeys) * (kTaKeys / 32);  // words read later
+    const int n = min(max(a.n_sel[row], 0), a.top_k);
+    const int32_t *sel = a.idx + row * a.top_k;
+    const int per = div_up(n, kMaskThreads);
+    for (int w0 = 0; w0 < end; w0 += kMaskKeys / 32) {
+        const int words = min(kMaskKeys / 32, end - w0);
+        __syncthreads();
+        for (int i = tid; i < words; i += kMaskThreads) w[i] = 0u;
+        __syncthreads();
+        uint32_t bits = 0u;
+        int at = -1;
+        for (int e = tid * per; e < min(n, (tid + 1) * per); ++e) {
+            const int j = sel[e], wj = (j >> 5) - w0;
+            if (wj != at) {
+                if (bits && at >= 0 && at < words) atomicOr(&w[at], bits);
+                bits = 0u;
+                at = wj;
+            }
+            bits |= 1u << (j & 31);
+        }
+        if (bits && at >= 0 && at < words) atomicOr(&w[at], bits);
+        __syncthreads();
+        for (int i = tid; i < words; i += kMaskThreads) a.mask[row * a.pitch + w0 + i] = w[i];
+    }
+}
+
+// Workgroups per sequence and KV head: NW waves, one per (32 rows, query head).
+constexpr int kTaWaves = 8;
+static int tile_blocks(const Geometry &g) { return div_up(div_up(g.n_q, 32) * g.group, kTaWaves); }
 
 bool tile_attn_dense(const Geometry &g) { return g.n_q >= kTileAttnMinRows; }
 
 void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span) {
-    const long blocks = (long)g.batch * div_up(g.n_q, tile_rows(g.group)) * g.kv_heads;
+    const long blocks = (long)g.batch * tile_blocks(g) * g.kv_heads;
     long want = (kTileAttnWorkgroups + blocks - 1) / blocks;
     if (want > max_splits) want = max_splits;
     const int tiles = div_up(g.max_len, kTaKeys);
@@ -351,6 +437,8 @@ void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span) {
     span = div_up(tiles, (int)want) * kTaKeys;
     splits = div_up(g.max_len, span);
 }
+
+static int mask_words(const Geometry &g) { return div_up(g.max_len, kTaKeys) * (kTaKeys / 32); }
 
 hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cache,
                             const void *v_cache, const int32_t *page_table,
@@ -364,7 +452,7 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
     a.page_table = page_table;
     a.seq_lens = seq_lens;
     a.q_pos = q_pos;
-    a.mask = reinterpret_cast<const uint64_t *>(mask);
+    a.mask = mask;
     a.out = static_cast<uint16_t *>(out);
     a.lse = lse;
     a.part_o = part_o;
@@ -377,33 +465,66 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
     a.causal = g.causal;
     a.kv_heads = g.kv_heads;
     a.q_heads = g.q_heads;
-    a.row_blocks = div_up(g.n_q, tile_rows(g.group));
+    a.group = g.group;
+    a.row_blocks = tile_blocks(g);
     a.splits = splits;
     a.span = span;
-    a.mask_blocks = div_up(g.n_q, 32);
-    a.mask_pitch = div_up(g.max_len, kTaKeys) * (kTaKeys / 2);
+    a.mask_pitch = mask_words(g);
     a.scale_log2 = g.softmax_scale * 1.4426950408889634f;
     const size_t blocks = (size_t)g.batch * a.row_blocks * g.kv_heads * splits;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks);
     const bool paged = g.page_shift >= 0;
-#define TILE_ATTN(G, RB)                                                                        \
-    if (mask && paged) tile_attn_kernel<G, RB, true, true><<<grid, dim3(64 * G * RB), 0, stream>>>(a); \
-    else if (mask) tile_attn_kernel<G, RB, false, true><<<grid, dim3(64 * G * RB), 0, stream>>>(a);    \
-    else if (paged) tile_attn_kernel<G, RB, true, false><<<grid, dim3(64 * G * RB), 0, stream>>>(a);   \
-    else tile_attn_kernel<G, RB, false, false><<<grid, dim3(64 * G * RB), 0, stream>>>(a);             \
-    break
-    switch (g.group) {
-        case 1: TILE_ATTN(1, 4);
-        case 2: TILE_ATTN(2, 2);
-        case 4: TILE_ATTN(4, 1);
-        case 5: TILE_ATTN(5, 1);
-        case 8: TILE_ATTN(8, 1);
-        default: return hipErrorInvalidValue;
-    }
-#undef TILE_ATTN
+    const dim3 block(64 * kTaWaves);
+    if (mask && paged) tile_attn_kernel<kTaWaves, true, true><<<grid, block, 0, stream>>>(a);
+    else if (mask) tile_attn_kernel<kTaWaves, false, true><<<grid, block, 0, stream>>>(a);
+    else if (paged) tile_attn_kernel<kTaWaves, true, false><<<grid, block, 0, stream>>>(a);
+    else tile_attn_kernel<kTaWaves, false, false><<<grid, block, 0, stream>>>(a);
     return hipGetLastError();
+}
+
+// Masked tiles cost every key of a row, gathers only the selected ones, so the
+// line lies where a row selects about a tenth of its keys (groups of 4; the
+// gather serves a whole group, the tiles pay per query head).  Both sides are
+// priced with what they measured: a workgroup's tile step (8 waves x 64 keys, one
+// workgroup per CU) 3.1 us; a gather 22 + 1.4 G ps per (row, KV head, selected
+// token).  Per layer of 4096 rows x 16384 keys, k = 2048, 32 / 8 heads: gathers
+// 1.85 ms, tiles 1.2; 4096 x 32768: 1.95 against 2.6.
+bool tile_attn_masked(const Geometry &g, size_t scratch_floats) {
+    if ((size_t)g.rows * mask_words(g) > scratch_floats) return false;
+    if (g.n_q < kTileAttnMinRows) return false;
+    const double wgs = (double)g.batch * tile_blocks(g) * g.kv_heads;
+    const int half = g.max_len / 2, mean = g.max_len - g.n_q / 2;  // causal: the last n_q rows
+    const double keys = wgs > 256 && g.causal ? (mean > half ? mean : half) : g.max_len;
+    const double rounds = wgs > 256 ? wgs / 256 + 0.3 : 1.0;  // the last round is partly empty
+    const double tiles_us = rounds * (keys / kTaKeys) * 3.1;
+    const double sel = g.top_k < keys ? g.top_k : keys;
+    const double gather_us = (double)g.rows * g.kv_heads * sel * (22.0 + 1.4 * g.group) * 1e-6;
+    return 1.1 * tiles_us < gather_us;
+}
+
+hipError_t launch_attn_mask(const Geometry &g, const int32_t *idx, const int32_t *n_sel,
+                            const int32_t *seq_lens, uint32_t *mask, hipStream_t stream) {
+    MaskArgs a;
+    a.idx = idx;
+    a.n_sel = n_sel;
+    a.seq_lens = seq_lens;
+    a.mask = mask;
+    a.n_q = g.n_q;
+    a.max_len = g.max_len;
+    a.top_k = g.top_k;
+    a.pitch = mask_words(g);
+    attn_mask_kernel<<<dim3((unsigned)g.rows), dim3(kMaskThreads), 0, stream>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_masked_attn(const Geometry &g, const void *q, const void *k_cache,
+                              const void *v_cache, const int32_t *page_table,
+                              const int32_t *seq_lens, const int32_t *q_pos, const uint32_t *mask,
+                              void *out, float *lse, hipStream_t stream) {
+    return launch_tile_attn(g, q, k_cache, v_cache, page_table, seq_lens, q_pos, mask, 1,
+                            div_up(g.max_len, kTaKeys) * kTaKeys, out, lse, nullptr, nullptr, stream);
 }
 
 hipError_t take_device_error_tile_attn(uint32_t *bits) { return take_source_device_error(bits); }

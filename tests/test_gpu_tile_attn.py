@@ -81,3 +81,37 @@ def test_values_not_finite_stay_with_the_rows_that_see_them(which, bad):
         assert not np.isfinite(o[0, 20:, :, 5]).any()
         assert np.isfinite(np.delete(o[0, 20:], 5, axis=-1)).all()
         assert np.isfinite(ls).all()
+
+
+@pytest.mark.parametrize("qh,kvh,ps", [(32, 8, 0), (20, 4, 64), (16, 8, 16), (64, 8, 64)])
+@pytest.mark.parametrize("top_k", [300, 950])
+def test_step_with_selection_masks(qh, kvh, ps, top_k):
+    """Chunked prefill over few keys: every layer attends in tiles with a
+    selection mask.  Rows that select everything (words of ones, and a word cut
+    at the row's own position), a part, or nothing (rows before a shorter
+    sequence's first token)."""
+    from tests.test_gpu_decode_step import _check_step
+    w = inputs.small_workload(batch=2, lens=(1000, 610), n_q=1000, causal=True,
+                              q_pos0=(0, 610 - 1000), q_heads=qh, kv_heads=kvh, page_size=ps,
+                              top_k=top_k, n_layers=2, wid=85)
+    _check_step(w, inputs.make_inputs(w), [1], f"masked tiles k={top_k} Hq={qh} Hkv={kvh}")
+
+
+@pytest.mark.parametrize("ps", [0, 64])
+def test_step_selection_excludes_values_not_finite(ps):
+    """An infinite value of one token reaches the rows that select it, no other."""
+    from tests.test_gpu_decode_step import _gpu_step
+    w = inputs.small_workload(batch=1, lens=(960,), n_q=960, causal=True, q_pos0=(0,), top_k=400,
+                              page_size=ps, n_layers=1, wid=86)
+    x = inputs.make_inputs(w)
+    at = (int(x["page_table"][0, 500 // ps]), 500 % ps) if ps else (0, 500)
+    x["v_cache"][at][:, 7] = inputs.bf16_bits_from_f32(np.float32([np.inf]))[0]
+    out, lse, idx, ns = _gpu_step(w, x, 1)
+    has = (idx[0] == 500).any(-1)
+    assert has[500:].any() and not has.all() and not has[500:].all()
+    o = inputs.f32_from_bf16_bits(out[0, 0])
+    assert np.isfinite(o[~has]).all() and np.isfinite(lse).all()
+    assert np.isposinf(o[has][:, :, 7]).all()
+    ro, rl = orc.sparse_attn(orc.shape_of(w), x["q_layers"][0], x["k_cache"], x["v_cache"], idx,
+                             ns, x["page_table"])
+    U.compare_attn(out[0], lse[0], ro, rl, mask_rows=~has[None])
