@@ -166,13 +166,16 @@ hipError_t launch_dense_attn(const Geometry &g, const void *q, const void *k_cac
 size_t dense_partial_floats(const Geometry &g);
 
 // ---- tile_attn.hip ----
-// Query rows per sequence from which dense attention runs over key tiles shared
-// by a block of rows (16 rows, half of a block's 32, against one gather per row:
-// 2000 keys 15.1 us each way, 32768 keys 41 against 112, 8 x 4096 keys 43 against
-// 101; from 24 rows on faster everywhere measured), and the workgroups aimed at
-// (two per CU, by splitting the key range).
+// Dense attention runs over key tiles shared by a block of rows from 16 query
+// rows per sequence (half of a block's 32; against one gather per row, 32 / 8
+// heads: 16 rows x 32768 keys 48 us against 112, 8 sequences of 4096 keys 49
+// against 100, 2000 keys 14 each way) and 4e5 keys over all (row, KV head) pairs
+// (64 rows x 600 keys x 8: 3.1e5, 18.1 us against 15.1; 32 x 2000 x 8: 5.1e5, 16.4
+// against 17.3; 500 x 600 x 8: 2.4e6, 25 against 38).  Workgroups aimed at (by
+// splitting the key range): one per CU.
 constexpr int kTileAttnMinRows = 16;
-constexpr int kTileAttnWorkgroups = 512;
+constexpr double kTileAttnMinKeys = 4e5;
+constexpr int kTileAttnWorkgroups = 256;
 bool tile_attn_dense(const Geometry &g);
 // Key ranges per row (at most max_splits) and keys per range.
 void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span);

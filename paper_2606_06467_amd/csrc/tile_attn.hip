@@ -425,14 +425,17 @@ __global__ __launch_bounds__(kMaskThreads) void attn_mask_kernel(MaskArgs a) {
 constexpr int kTaWaves = 8;
 static int tile_blocks(const Geometry &g) { return div_up(div_up(g.n_q, 32) * g.group, kTaWaves); }
 
-bool tile_attn_dense(const Geometry &g) { return g.n_q >= kTileAttnMinRows; }
+bool tile_attn_dense(const Geometry &g) {
+    return g.n_q >= kTileAttnMinRows &&
+           (double)g.rows * g.kv_heads * g.max_len >= kTileAttnMinKeys;
+}
 
 void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span) {
     const long blocks = (long)g.batch * tile_blocks(g) * g.kv_heads;
     long want = (kTileAttnWorkgroups + blocks - 1) / blocks;
     if (want > max_splits) want = max_splits;
     const int tiles = div_up(g.max_len, kTaKeys);
-    if (want > tiles / 4) want = tiles / 4;  // at least four tiles each
+    if (want > tiles / 2) want = tiles / 2;  // at least two tiles each
     if (want < 1) want = 1;
     span = div_up(tiles, (int)want) * kTaKeys;
     splits = div_up(g.max_len, span);

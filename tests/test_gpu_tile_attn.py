@@ -14,8 +14,9 @@ from tests.test_gpu_dense import _case, _full_sets
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nq,n,ps", [(16, 63, 0), (31, 64, 16), (32, 65, 0), (33, 127, 64),
-                                     (65, 129, 0), (130, 1000, 64)])
+# at least 4e5 keys over all (row, KV head) pairs, so that the tiles are taken
+@pytest.mark.parametrize("nq,n,ps", [(17, 4161, 0), (32, 2113, 16), (33, 2048, 0), (97, 769, 64),
+                                     (250, 321, 0), (288, 288, 64)])
 @pytest.mark.parametrize("qh,kvh", [(4, 4), (4, 2), (32, 8), (10, 2), (16, 2)])
 def test_tile_edges(nq, n, ps, qh, kvh):
     """Causal rows that end with their sequence; the second sequence is shorter
@@ -35,11 +36,11 @@ def test_not_causal_split_by_key_range(nq, n):
 
 def test_large_logits():
     """Logits of hundreds: the running maximum moves far, in both directions."""
-    w = inputs.small_workload(batch=1, lens=(400,), n_q=40, causal=True, q_pos0=(360,),
+    w = inputs.small_workload(batch=1, lens=(1300,), n_q=40, causal=True, q_pos0=(1260,),
                               n_layers=1, wid=83)
     x = inputs.make_inputs(w, layers=[0])
     k = inputs.f32_from_bf16_bits(x["k_cache"])
-    k *= np.linspace(-30, 30, 400)[None, :, None, None]
+    k *= np.linspace(-30, 30, 1300)[None, :, None, None]
     x["k_cache"] = inputs.bf16_bits_from_f32(k)
     _run_and_compare(w, x)
 
@@ -68,14 +69,14 @@ def _run_and_compare(w, x, mask_rows=None):
 @pytest.mark.parametrize("which", ["k_cache", "v_cache"])
 def test_values_not_finite_stay_with_the_rows_that_see_them(which, bad):
     """A token whose key or value is not finite changes no row before it."""
-    w = inputs.small_workload(batch=1, lens=(300,), n_q=70, causal=True, q_pos0=(230,),
+    w = inputs.small_workload(batch=1, lens=(800,), n_q=70, causal=True, q_pos0=(730,),
                               n_layers=1, wid=84)
     x = inputs.make_inputs(w, layers=[0])
     x["k_cache"] = x["k_cache"].copy()
     x["v_cache"] = x["v_cache"].copy()
-    x[which][0, 250, :, 5] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
+    x[which][0, 750, :, 5] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
     before = np.zeros((1, 70), bool)
-    before[0, :20] = True  # positions 230 .. 249
+    before[0, :20] = True  # positions 730 .. 749
     o, ls = _run_and_compare(w, x, mask_rows=before)
     if which == "v_cache":  # the others carry it, in that dimension alone
         assert not np.isfinite(o[0, 20:, :, 5]).any()
