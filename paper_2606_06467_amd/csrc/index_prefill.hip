@@ -537,6 +537,19 @@ static hipError_t launch_prefill(const Geometry &g, const PrefillArgs &a, hipStr
     return hipGetLastError();
 }
 
+// Enough workgroups for the chip when a pass has few key blocks: split the
+// query tiles of each key block over ranges, which also evens out causal rows
+// (the last key blocks see few of them).  Writing the scores of 2 x 4096 causal
+// rows over 4096 keys took 265 us on the 32 workgroups of one range and 45
+// on 1024; of 32768 over 32768 2.07 ms on 128 and 0.85 on 1024 (512 and 2048
+// workgroups within 1%).
+static int prefill_qsplit(const Geometry &g, int kblocks) {
+    const int ntiles = div_up(g.n_q, 16);
+    int qsplit = 1;
+    while ((long)g.batch * kblocks * qsplit < 1024 && qsplit * 4 <= ntiles) qsplit *= 2;
+    return qsplit;
+}
+
 hipError_t launch_index_prefill(const Geometry &g, const void *q_idx, const void *k_idx,
                                 const int32_t *page_table, const int32_t *seq_lens,
                                 const int32_t *q_pos, float *scores, uint32_t *attn_tickets,
@@ -547,16 +560,8 @@ hipError_t launch_index_prefill(const Geometry &g, const void *q_idx, const void
     a.row_stride = g.max_len;
     a.kblocks = div_up(g.max_len, kPfKeys);
     a.vec_store = (g.max_len % 4) == 0;
+    a.qsplit = prefill_qsplit(g, a.kblocks);
     return launch_prefill(g, a, stream);
-}
-
-// Enough workgroups for the chip when a pass has few key blocks: split the
-// query tiles of each key block over ranges.
-static int prefill_qsplit(const Geometry &g, int kblocks) {
-    const int ntiles = div_up(g.n_q, 16);
-    int qsplit = 1;
-    while ((long)g.batch * kblocks * qsplit < 1024 && qsplit * 4 <= ntiles) qsplit *= 2;
-    return qsplit;
 }
 
 hipError_t launch_index_prefill_sample(const Geometry &g, const void *q_idx, const void *k_idx,

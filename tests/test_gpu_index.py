@@ -78,6 +78,8 @@ def test_full_size_ragged_paged():
     (2, (4000, 1500), 150, False, None, 64),        # two query blocks, paged
     (1, (2049,), 32, False, None, 0),               # smallest row count on this path
     (3, (1100, 17, 2200), 45, True, (1055, 0, 900), 16),  # short causal rows, small pages
+    (1, (1000,), 1000, True, (0,), 0),               # few key blocks: query tiles in 8 ranges
+    (2, (257, 255), 333, False, None, 16),           # ... in ranges of unequal length
 ])
 def test_many_rows_matrix_cores(batch, lens, n_q, causal, q_pos0, page):
     w = inputs.small_workload(batch=batch, lens=lens, n_q=n_q, causal=causal, q_pos0=q_pos0,
