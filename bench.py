@@ -409,8 +409,8 @@ def run_kd(args, w) -> int:
         "tokens_per_s": round(w.batch * w.n_q / (ms_per_step * 1e-3), 1),
         "ms_per_step_with_forward_lse": round(ms_fwd_lse, 3),
         "phases_ms": {"statistics_kernel": round(lse_ms, 3), "target_kernel": round(tgt_ms, 3),
-                      "index_scores": round(scores_ms, 3), "loss_rows": round(rows_ms, 3),
-                      "gradients": round(grad_ms, 3)},
+                      "row_statistics": round(scores_ms, 3), "dq_and_loss": round(rows_ms, 3),
+                      "dk": round(grad_ms, 3)},
         # the kernel with the largest share: both target-pass kernels make one
         # logit product over every (layer, head, row, key)
         "roofline": roofline_mfma(main_k, w, cnt["logit_flops"], kern[main_k]),

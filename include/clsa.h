@@ -306,8 +306,9 @@ clsa_status clsa_get_device_error(uint32_t *bits);
  * after it (before its split merge, if any).  clsa_kd_target records
  * events[0] before its statistics kernel, events[1] between it and the target
  * kernel and events[2] after the target kernel; clsa_kd_loss records events[0]
- * before the index scores, events[1] after them, events[2] after the loss
- * kernels and events[3] after the gradient kernels.  The handles are kept, not
+ * before the row statistics, events[1] after them, events[2] after the
+ * index-query gradient and the loss (one pass makes both) and events[3] after
+ * the index-key gradient.  The handles are kept, not
  * copied: they must stay valid while the hook is on.  n == 0 (events may be
  * NULL) switches the hook off.  Any other n, or a NULL handle, is
  * CLSA_ERR_INVALID_ARG and leaves the hook as it was. */

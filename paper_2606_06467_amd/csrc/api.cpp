@@ -616,6 +616,7 @@ clsa_status clsa_get_device_error(uint32_t *bits) {
     CLSA_TRY(from_hip(clsa::take_device_error_sparse_attn(&v)));
     CLSA_TRY(from_hip(clsa::take_device_error_tile_attn(&v)));
     CLSA_TRY(from_hip(clsa::take_device_error_kd(&v)));
+    CLSA_TRY(from_hip(clsa::take_device_error_kd_loss(&v)));
     *bits = v;
     return CLSA_OK;
 }

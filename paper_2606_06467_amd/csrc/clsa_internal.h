@@ -57,6 +57,7 @@ hipError_t take_device_error_index_prefill(uint32_t *bits);
 hipError_t take_device_error_topk(uint32_t *bits);
 hipError_t take_device_error_sparse_attn(uint32_t *bits);
 hipError_t take_device_error_kd(uint32_t *bits);
+hipError_t take_device_error_kd_loss(uint32_t *bits);
 
 // ---- index_decode.hip ----
 // coarse_hist: [rows, kCoarseBins], zero on entry, or NULL for no histogram.
@@ -218,8 +219,10 @@ hipError_t launch_kd_target(const Geometry &g, int n_layers, const void *q_layer
                             const int32_t *seq_lens, const int32_t *q_pos, const float *lse_in,
                             float *abar, float *lse2, hipStream_t stream,
                             hipEvent_t between = nullptr);
+// ---- kd_loss.hip ----
 // Eq. 6 loss and its gradient: workspace of kd_loss_ws_floats floats; the
-// events, if not null, are recorded after the index scores and after the loss.
+// events, if not null, are recorded after the row statistics and after dq and
+// the loss (before dk).
 bool kd_loss_supported(const Geometry &g);
 size_t kd_loss_ws_floats(const Geometry &g);
 hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_idx,

@@ -1,5 +1,5 @@
 // Training side of the shared indexer (Section 2.2): the distillation target
-// of Eq. 5 and the KL loss of Eq. 6 with its gradient.
+// of Eq. 5 (its loss, Eq. 6, is in kd_loss.hip).
 //
 // Eq. 5: abar[b,t,j] = (1 / (L * Hq)) * sum over layers l and query heads h of
 // softmax_j(scale * q_l[b,t,h] . K[b,j,g(h)]) over the valid keys of row (b,t),
@@ -19,17 +19,6 @@
 //     KV head are loaded once for all layers and heads of its group, the four
 //     waves of a workgroup share their rows' query operands, and abar is
 //     written once, with no atomics.
-// Eq. 6: P = abar (a constant), Q = softmax(I_t) over the valid keys, I the
-// unscaled index scores of Eq. 3 (computed by the indexer kernels); the loss
-// is the mean over rows with at least one key of KL(P || Q), and
-// dL/dI = (Q - P) / n_rows:
-//   * kd_rows_kernel: per row, the log-sum-exp of I, the row's KL term and
-//     Q - P, written over the scores;
-//   * kd_loss_kernel: n_rows and the mean of the row terms (summed in double
-//     in a fixed order);
-//   * kd_dq_kernel / kd_dk_kernel: dq = dL/dI K_idx and dk = dL/dI^T Q_idx,
-//     fp32 matrix-core products tiled through LDS (64 x 64 outputs per
-//     workgroup, 32-deep steps).
 #include "clsa_internal.h"
 #include "device_common.h"
 
@@ -42,7 +31,6 @@ constexpr float kKdLog2e = 1.4426950408889634f;
 constexpr float kKdLn2 = 0.6931471805599453f;
 constexpr int kKdDim = 128;  // attention head dimension
 constexpr int kKdTile = 64;  // rows and keys per target tile
-constexpr int kIdxDim = 256; // index vector width
 
 struct KdArgs {
     const uint16_t *q_layers;  // [L, rows, Hq, 128]
@@ -461,297 +449,6 @@ __global__ __launch_bounds__(256) void kd_target_kernel(KdArgs a) {
     }
 }
 
-struct KdLossArgs {
-    const float *abar;         // [rows, max_len]
-    float *dI;                 // [rows, max_len]: index scores in, Q - P out
-    float *row_kl;             // [rows]
-    float *stats;              // [0] = 1 / n_rows (0 when none), [1] = n_rows
-    int32_t *step_max;         // [B, ceil(n_q / 32)]: most keys of any row of each 32-row step
-    float *loss;
-    const uint16_t *q_idx;     // [rows, 256]
-    const uint16_t *k_idx;     // index-key cache
-    float *dq, *dk;
-    const int32_t *page_table, *seq_lens, *q_pos;
-    int n_q, rows, max_len, page_shift, max_pages, causal, row_tiles, key_tiles;
-};
-
-// One workgroup of 256 threads per row.
-__global__ __launch_bounds__(256) void kd_rows_kernel(KdLossArgs a) {
-    __shared__ float red_m[4], red_s[4];
-    const int row = blockIdx.x, b = row / a.n_q;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int n = valid_keys(a.seq_lens, a.q_pos, a.causal, b, row, a.max_len);
-    if (n == 0) {  // uniform: no keys, no loss term
-        if (tid == 0) a.row_kl[row] = 0.0f;
-        return;
-    }
-    float *s = a.dI + (size_t)row * a.max_len;
-    const float *p = a.abar + (size_t)row * a.max_len;
-    float m = -INFINITY, sum = 0.0f;  // log2 units
-    for (int j = tid; j < n; j += 256) {
-        const float x = s[j] * kKdLog2e;
-        if (x > m) {
-            sum = sum * exp2f(m - x) + 1.0f;
-            m = x;
-        } else {
-            sum += exp2f(x - m);
-        }
-    }
-    const float wm = wave_max(m);
-    const float ws = wave_sum(sum > 0.0f ? sum * exp2f(m - wm) : 0.0f);
-    if ((tid & 63) == 0) {
-        red_m[wave] = wm;
-        red_s[wave] = ws;
-    }
-    __syncthreads();
-    const float bm = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
-    float bs = 0.0f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) bs += red_s[w] > 0.0f ? red_s[w] * exp2f(red_m[w] - bm) : 0.0f;
-    const float lse2 = bm + log2f(bs);
-    float kl = 0.0f;  // log2 units
-    for (int j = tid; j < n; j += 256) {
-        const float z = fmaf(s[j], kKdLog2e, -lse2);
-        const float pj = p[j];
-        if (pj > 0.0f) kl += pj * (log2f(pj) - z);
-        s[j] = exp2f(z) - pj;
-    }
-    kl = wave_sum(kl);
-    __syncthreads();  // red_s reads above are done
-    if ((tid & 63) == 0) red_s[wave] = kl;
-    __syncthreads();
-    if (tid == 0) a.row_kl[row] = (red_s[0] + red_s[1] + red_s[2] + red_s[3]) * kKdLn2;
-}
-
-// One workgroup: n_rows, 1 / n_rows and the mean row term.
-__global__ __launch_bounds__(256) void kd_loss_kernel(KdLossArgs a) {
-    __shared__ double red_t[256];
-    __shared__ int red_c[256];
-    const int tid = threadIdx.x;
-    double tot = 0.0;
-    int cnt = 0;
-    for (int r = tid; r < a.rows; r += 256) {
-        tot += (double)a.row_kl[r];
-        cnt += valid_keys(a.seq_lens, a.q_pos, a.causal, r / a.n_q, r, a.max_len) > 0;
-    }
-    red_t[tid] = tot;
-    red_c[tid] = cnt;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) {
-            red_t[tid] += red_t[tid + w];
-            red_c[tid] += red_c[tid + w];
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        const int nr = red_c[0];
-        a.loss[0] = nr > 0 ? (float)(red_t[0] / nr) : 0.0f;
-        a.stats[0] = nr > 0 ? 1.0f / (float)nr : 0.0f;
-        a.stats[1] = (float)nr;
-    }
-}
-
-constexpr int kGemmDepth = 32;  // contraction steps per LDS stage
-constexpr int kRowPitch = 36;   // [row][key] staging: the MFMA reads (16 rows x 4 keys) and the
-                                // row-contiguous stores both fall on distinct banks
-constexpr int kColPitch = 80;   // [k][column] staging: the MFMA reads (4 k x 16 columns) fall
-                                // on distinct banks
-
-// 8 bf16 -> 8 floats stored at dst (16-byte aligned).
-__device__ __forceinline__ void kd_store8(float *dst, u32x4 v) {
-    float4 lo = make_float4(bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y));
-    float4 hi = make_float4(bf16_lo(v.z), bf16_hi(v.z), bf16_lo(v.w), bf16_hi(v.w));
-    *reinterpret_cast<float4 *>(dst) = lo;
-    *reinterpret_cast<float4 *>(dst + 4) = hi;
-}
-
-// The gradient products run on v_mfma_f32_16x16x4_f32 (fp32 operands, so the
-// bf16 keys and queries enter exactly and dL/dI keeps its fp32 bits): lane l
-// supplies A[l & 15][l >> 4] and B[l >> 4][l & 15] and receives C rows
-// 4 * (l >> 4) + r of column l & 15.  A workgroup computes 64 x 64 outputs,
-// each wave 16 rows x 64 columns (four column tiles), 32 contraction steps per
-// LDS stage.
-
-// step_max[b, s] = the most valid keys of any row of rows 32 s .. 32 s + 31 of
-// sequence b.  One thread per (sequence, step).
-__global__ __launch_bounds__(256) void kd_step_max_kernel(KdLossArgs a, int total) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= total) return;
-    const int nsteps = div_up(a.n_q, kGemmDepth);
-    const int b = i / nsteps, r0 = (i % nsteps) * kGemmDepth;
-    int m = 0;
-    for (int k = 0; k < kGemmDepth && r0 + k < a.n_q; ++k)
-        m = max(m, valid_keys(a.seq_lens, a.q_pos, a.causal, b, b * a.n_q + r0 + k, a.max_len));
-    a.step_max[i] = m;
-}
-
-// dq[b,t,c] = (1 / n_rows) sum_{j < n(b,t)} dI[b,t,j] k_idx[b,j,c].
-// grid: ((b * row_tiles + tile) * 4 + column tile), 64 rows x 64 columns each.
-__global__ __launch_bounds__(256) void kd_dq_kernel(KdLossArgs a) {
-    __shared__ __align__(16) float As[64][kRowPitch];           // [row][key]
-    __shared__ __align__(16) float Bs[kGemmDepth][kColPitch];   // [key][column]
-    __shared__ int s_n[64];
-    int x = blockIdx.x;
-    const int c0 = (x & 3) * 64;
-    x >>= 2;
-    const int tile = x % a.row_tiles, b = x / a.row_tiles;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col = lane & 15, kq = lane >> 4;
-    const int t0 = tile * 64;
-    if (tid < 64) {
-        const int t = t0 + tid;
-        s_n[tid] = t < a.n_q ? valid_keys(a.seq_lens, a.q_pos, a.causal, b, b * a.n_q + t, a.max_len)
-                             : 0;
-    }
-    __syncthreads();
-    int nmax = 0;
-    for (int i = 0; i < 64; ++i) nmax = max(nmax, s_n[i]);
-    f32x4 acc[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int ak = tid & 31, ai = tid >> 5;        // A loads: key ak, rows ai + 8 * step
-    const int bk = tid >> 3, bc = (tid & 7) * 8;   // B loads: key bk, columns bc .. bc + 7
-    int nrow[8];
-#pragma unroll
-    for (int st = 0; st < 8; ++st) nrow[st] = s_n[ai + 8 * st];
-    // one stage's operands, read into registers a stage ahead of their use
-    float av_n[8];
-    u32x4 kv_n;
-    auto fetch = [&](int j0) {
-        const int j = j0 + ak;
-#pragma unroll
-        for (int st = 0; st < 8; ++st)
-            av_n[st] = j < nrow[st]
-                           ? a.dI[((size_t)b * a.n_q + t0 + ai + 8 * st) * a.max_len + j]
-                           : 0.0f;
-        const int jb = j0 + bk;
-        kv_n = u32x4{0u, 0u, 0u, 0u};
-        if (jb < nmax)
-            kv_n = *reinterpret_cast<const u32x4 *>(
-                a.k_idx + token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b, jb,
-                                       kIdxDim) +
-                c0 + bc);
-    };
-    if (nmax > 0) fetch(0);
-    for (int j0 = 0; j0 < nmax; j0 += kGemmDepth) {
-#pragma unroll
-        for (int st = 0; st < 8; ++st) As[ai + 8 * st][ak] = av_n[st];
-        kd_store8(&Bs[bk][bc], kv_n);
-        __syncthreads();
-        if (j0 + kGemmDepth < nmax) fetch(j0 + kGemmDepth);
-#pragma unroll
-        for (int kk = 0; kk < kGemmDepth; kk += 4) {
-            const float av = As[wave * 16 + col][kk + kq];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, Bs[kk + kq][ct * 16 + col],
-                                                               acc[ct], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    const float inv_n = a.stats[0];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int t = t0 + wave * 16 + 4 * kq + r;
-        if (t < a.n_q) {
-            float *dst = a.dq + ((size_t)b * a.n_q + t) * kIdxDim + c0 + col;
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) dst[ct * 16] = acc[ct][r] * inv_n;
-        }
-    }
-}
-
-// dk[b,j,c] = (1 / n_rows) sum_{t : j < n(b,t)} dI[b,t,j] q_idx[b,t,c], for j < seq_lens[b].
-// grid: ((b * key_tiles + tile) * 4 + column tile), 64 keys x 64 columns each.
-__global__ __launch_bounds__(256) void kd_dk_kernel(KdLossArgs a) {
-    __shared__ __align__(16) float As[kGemmDepth][kColPitch];  // [row][key]
-    __shared__ __align__(16) float Bs[kGemmDepth][kColPitch];  // [row][column]
-    int x = blockIdx.x;
-    const int c0 = (x & 3) * 64;
-    x >>= 2;
-    const int tile = x % a.key_tiles, b = x / a.key_tiles;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col = lane & 15, kq = lane >> 4;
-    const int j0 = tile * 64;
-    const int len = clamp_len(a.seq_lens[b], a.max_len);
-    if (j0 >= len) return;  // uniform: no token of this tile is written
-    f32x4 acc[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int ai = tid & 63, ak = tid >> 6;        // A loads: key ai, rows ak + 4 * step
-    const int bk = tid >> 3, bc = (tid & 7) * 8;   // B loads: row bk, columns bc .. bc + 7
-    // one step's operands (32 rows from r0), read into registers a step ahead
-    float av_n[8];
-    u32x4 qv_n;
-    auto fetch = [&](int r0) {
-#pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            const int t = r0 + ak + 4 * st;
-            const int nk = t < a.n_q ? valid_keys(a.seq_lens, a.q_pos, a.causal, b, b * a.n_q + t,
-                                                  a.max_len)
-                                     : 0;
-            av_n[st] = j0 + ai < nk ? a.dI[((size_t)b * a.n_q + t) * a.max_len + j0 + ai] : 0.0f;
-        }
-        const int t = r0 + bk;
-        qv_n = u32x4{0u, 0u, 0u, 0u};
-        if (t < a.n_q)
-            qv_n = *reinterpret_cast<const u32x4 *>(a.q_idx + ((size_t)b * a.n_q + t) * kIdxDim +
-                                                    c0 + bc);
-    };
-    // Only the steps with a row that sees one of the tile's keys contribute
-    // (in a causal sequence, those from the tile's own position on): 256 steps
-    // at a time, their per-step key maxima give an ordered list of the useful
-    // ones (wave ballots, so the summation order is fixed), and the loop runs
-    // over that list with the next step's operands in flight.
-    __shared__ int s_list[256];
-    __shared__ int s_wcnt[4];
-    const int nsteps = div_up(a.n_q, kGemmDepth);
-    const int32_t *smax = a.step_max + (size_t)b * nsteps;
-    for (int s0 = 0; s0 < nsteps; s0 += 256) {
-        const int st_i = s0 + tid;
-        const bool useful = st_i < nsteps && smax[st_i] > j0;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(useful);
-        const int before = __builtin_popcountll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) s_wcnt[wave] = __builtin_popcountll(m);
-        __syncthreads();
-        int off = 0;
-        for (int w = 0; w < wave; ++w) off += s_wcnt[w];
-        const int cnt = s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3];
-        if (useful) s_list[off + before] = st_i;
-        __syncthreads();
-        if (cnt > 0) fetch(s_list[0] * kGemmDepth);
-        for (int i = 0; i < cnt; ++i) {
-#pragma unroll
-            for (int st = 0; st < 8; ++st) As[ak + 4 * st][ai] = av_n[st];
-            kd_store8(&Bs[bk][bc], qv_n);
-            __syncthreads();
-            if (i + 1 < cnt) fetch(s_list[i + 1] * kGemmDepth);
-#pragma unroll
-            for (int kk = 0; kk < kGemmDepth; kk += 4) {
-                const float av = As[kk + kq][wave * 16 + col];
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct)
-                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, Bs[kk + kq][ct * 16 + col],
-                                                                   acc[ct], 0, 0, 0);
-            }
-            __syncthreads();  // As / Bs and s_list are rewritten next
-        }
-    }
-    const float inv_n = a.stats[0];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int j = j0 + wave * 16 + 4 * kq + r;
-        if (j < len) {
-            float *dst = a.dk + token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b,
-                                             j, kIdxDim) +
-                         c0 + col;
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) dst[ct * 16] = acc[ct][r] * inv_n;
-        }
-    }
-}
-
 static bool grid_fits(long long n) { return n >= 1 && n <= 0x7fffffffLL; }
 
 // Row blocks of 16 and key blocks of 256 for the target pass; the lane offsets
@@ -838,61 +535,6 @@ hipError_t launch_kd_target(const Geometry &g, int n_layers, const void *q_layer
         default: return hipErrorInvalidValue;
     }
 #undef KD_TGT
-    return hipGetLastError();
-}
-
-bool kd_loss_supported(const Geometry &g) {
-    return grid_fits((long long)g.batch * div_up(g.n_q, 64) * 4) &&
-           grid_fits((long long)g.batch * div_up(g.max_len, 64) * 4);
-}
-
-size_t kd_loss_ws_floats(const Geometry &g) {
-    // scores / dL/dI, row terms, 2 statistics, per-step key maxima (int32)
-    return (size_t)g.rows * g.max_len + g.rows + 2 + (size_t)g.batch * div_up(g.n_q, 32);
-}
-
-hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_idx,
-                          const void *k_idx, const int32_t *page_table, const int32_t *seq_lens,
-                          const int32_t *q_pos, float *loss, float *dq, float *dk, float *ws,
-                          hipStream_t stream, hipEvent_t after_scores, hipEvent_t after_loss) {
-    if (!kd_loss_supported(g)) return hipErrorInvalidValue;
-    KdLossArgs a;
-    a.abar = abar;
-    a.dI = ws;
-    a.row_kl = ws + (size_t)g.rows * g.max_len;
-    a.stats = a.row_kl + g.rows;
-    a.step_max = reinterpret_cast<int32_t *>(a.stats + 2);
-    a.loss = loss;
-    a.q_idx = static_cast<const uint16_t *>(q_idx);
-    a.k_idx = static_cast<const uint16_t *>(k_idx);
-    a.dq = dq;
-    a.dk = dk;
-    a.page_table = page_table;
-    a.seq_lens = seq_lens;
-    a.q_pos = q_pos;
-    a.n_q = g.n_q;
-    a.rows = g.rows;
-    a.max_len = g.max_len;
-    a.page_shift = g.page_shift;
-    a.max_pages = g.max_pages;
-    a.causal = g.causal;
-    a.row_tiles = div_up(g.n_q, 64);
-    a.key_tiles = div_up(g.max_len, 64);
-    // The scores of Eq. 3 for every valid (row, key), then the row terms in place.
-    hipError_t e = index_uses_mfma(g)
-                       ? launch_index_prefill(g, q_idx, k_idx, page_table, seq_lens, q_pos, a.dI,
-                                              nullptr, stream)
-                       : launch_index_scores(g, q_idx, k_idx, page_table, seq_lens, q_pos, a.dI,
-                                             nullptr, nullptr, stream);
-    if (e != hipSuccess) return e;
-    if (after_scores && hipEventRecord(after_scores, stream) != hipSuccess) return hipErrorUnknown;
-    kd_rows_kernel<<<dim3(g.rows), dim3(256), 0, stream>>>(a);
-    kd_loss_kernel<<<dim3(1), dim3(256), 0, stream>>>(a);
-    if (after_loss && hipEventRecord(after_loss, stream) != hipSuccess) return hipErrorUnknown;
-    const int steps_total = g.batch * div_up(g.n_q, kGemmDepth);
-    kd_step_max_kernel<<<dim3(div_up(steps_total, 256)), dim3(256), 0, stream>>>(a, steps_total);
-    kd_dq_kernel<<<dim3((unsigned)(g.batch * a.row_tiles * 4)), dim3(256), 0, stream>>>(a);
-    kd_dk_kernel<<<dim3((unsigned)(g.batch * a.key_tiles * 4)), dim3(256), 0, stream>>>(a);
     return hipGetLastError();
 }
 

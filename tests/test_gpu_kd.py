@@ -421,3 +421,60 @@ def test_full_size_loss_last_key_tile():
     dd = np.abs(g_dk - r_k)
     U.log(f"    dk keys: max|d| {float(dd.max()):.2e}, worst err/bound {float((dd / e_k).max()):.3f}")
     assert np.all(dd <= e_k)
+
+
+@pytest.mark.parametrize("n,nq,q0,ps", [
+    ((1300, 700), 1300, (0, 700 - 1300), 0),      # key and row ranges, a padded short sequence
+    ((1090, 1090), 1090, (0, 0), 64),             # the same through a page table
+    ((1027, 3), 130, (900, -127), 0),             # rows that are no multiple of four floats apart
+    ((600, 0), 65, None, 0),                      # not causal: every row sees every key
+    ((70, 64), 1, None, 0),                       # one row
+])
+def test_loss_tiles_and_ranges(n, nq, q0, ps):
+    """Edges of the 128-vector blocks, the 64-vector tiles and the ranges of the
+    streamed side; the target a peaked random distribution."""
+    w = inputs.small_workload(batch=2, lens=n, n_q=nq, causal=q0 is not None, q_pos0=q0,
+                              page_size=ps, n_layers=1, q_heads=8, kv_heads=8, wid=101)
+    _loss_case(w, f"{n} x {nq} page {ps}", abar64=_peaked(w))
+
+
+def _peaked(w):
+    x = inputs.make_inputs(w, index_only=True)
+    nv = orc.valid_lens(orc.shape_of(w), x["seq_lens"], x["q_pos"])
+    z = np.random.default_rng(1011).standard_normal((w.batch, w.n_q, w.max_len)) * 2
+    e = np.exp(z) * (np.arange(w.max_len)[None, None, :] < nv[:, :, None])
+    return e / np.maximum(e.sum(-1, keepdims=True), 1e-300)
+
+
+@pytest.mark.parametrize("side", ["k_idx", "q_idx"])
+def test_loss_values_not_finite_stay_with_their_pairs(side):
+    """An index key (query) that is not finite reaches the gradients of the rows
+    (keys) it meets, no other."""
+    import torch
+    from paper_2606_06467_amd import binding as B
+    w = inputs.small_workload(batch=1, lens=(700,), n_q=700, causal=True, q_pos0=(0,), n_layers=1,
+                              q_heads=8, kv_heads=8, wid=102)
+    x = inputs.make_inputs(w)
+    ab = torch.from_numpy(_peaked(w).astype(np.float32)).cuda()
+    sh = U.shape_of(w)
+    got = []
+    for bad in (False, True):
+        if bad:
+            x[side] = x[side].copy()
+            x[side][0, 300, 1, 3] = inputs.bf16_bits_from_f32(np.float32([np.inf]))[0]
+        d = U.to_dev(x)
+        loss = torch.zeros(1, device="cuda")
+        dq, dk = (torch.zeros((1, 700, 256), device="cuda") for _ in range(2))
+        B.clsa_kd_loss(sh, ab, d["q_idx"], d["k_idx"], None, d["seq_lens"], d["q_pos"], loss, dq,
+                       dk, B.workspace(sh, B.CLSA_OP_KD_LOSS))
+        torch.cuda.synchronize()
+        got.append((dq.cpu().numpy()[0], dk.cpu().numpy()[0]))
+    (q0, k0), (q1, k1) = got
+    if side == "k_idx":   # rows before token 300 do not see it; its own row of dk is not finite
+        np.testing.assert_allclose(q1[:300], q0[:300], rtol=0, atol=1e-6 * np.abs(q0).max())
+        assert not np.isfinite(q1[300:]).all()
+    else:                 # row 300 sees keys 0 .. 300
+        keep = np.arange(700) != 300
+        np.testing.assert_allclose(q1[keep], q0[keep], rtol=0, atol=1e-6 * np.abs(q0).max())
+        np.testing.assert_allclose(k1[301:], k0[301:], rtol=0, atol=1e-6 * np.abs(k0).max())
+        assert not np.isfinite(k1[:301]).any()
