@@ -11,26 +11,20 @@
 //     are each issued as one unconditional batch (positions past the end are
 //     clamped and masked afterwards), so a workgroup waits for memory about
 //     three times instead of once per token;
-//   * the G query heads of the GQA group share those rows.  Two forms:
-//     - matrix-core form (MQK; contiguous caches, and chunked prefill with
-//       thousands of units): each wave's 16 K rows go through its own LDS rows
-//       into v_mfma_f32_16x16x32_bf16 against Q^T (heads padded to 16), and
-//       each wave keeps its own online softmax per head (base-2 exponentials;
-//       the four lanes of a head combine with permlane swaps) and its own
-//       weighted-V accumulators: no workgroup barrier per chunk; the wave
-//       states are merged by the log-sum-exp rule at the end.  The weighted V
-//       is a v_mfma_f32_16x16x16_bf16 product whose operands are the lane's
-//       own weights and V rows (the logits tile is ordered for that);
-//     - vector form (paged decode grids): each lane dots its 8 key values with
-//       the matching 8 values of every head (v_dot2_f32_bf16), a
-//       transpose-reduction over the 16 lanes leaves one (head, token) logit
-//       per lane, the logits go to LDS, and one wave per head takes the chunk
-//       maximum and sum, updates the running max / denominator and rescales
-//       (online softmax, shared by the workgroup);
-//     so a split of any length needs one pass;
-//   * in the vector form each lane accumulates weight x V for its 8 dimensions
-//     and G heads (v_dot2_f32_bf16).
-// The accumulators are then reduced over lanes and waves in LDS.  With one
+//   * the G query heads of the GQA group share those rows: each wave's 16 K rows
+//     go through its own LDS rows into v_mfma_f32_16x16x32_bf16 against Q^T
+//     (heads padded to 16), and each wave keeps its own online softmax per head
+//     (base-2 exponentials; the four lanes of a head combine with permlane
+//     swaps) and its own weighted-V accumulators: no workgroup barrier per
+//     chunk, so a split of any length needs one pass; the wave states are merged
+//     by the log-sum-exp rule at the end.  The weighted V is a
+//     v_mfma_f32_16x16x16_bf16 product whose operands are the lane's own weights
+//     and V rows (the logits tile is ordered for that).  (Paged decode grids had
+//     kept v_dot2 logits with a softmax shared through LDS and three barriers a
+//     chunk: 32 ragged sequences, k = 2048, 24 layers 1338 us against 1318 in this
+//     form; 4 x 20000 tokens, 8 layers 128 against 111 with groups of 4 and 163
+//     against 124 with groups of 8.)
+// The accumulators are then combined over the waves in LDS.  With one
 // split the workgroup writes the bf16 output and lse itself.  Otherwise it
 // writes fp32 partials (o, m, l), combined by the exact log-sum-exp rule: inside
 // the kernel by the last split of each (row, KV head) to arrive (inside
@@ -88,10 +82,6 @@ struct AttnArgs {
     // NULL: attn_merge_kernel runs as a second launch.
     uint32_t *tickets;
 };
-
-__host__ __device__ constexpr int pow2_at_least(int x) {
-    return x <= 1 ? 1 : 2 * pow2_at_least((x + 1) / 2);
-}
 
 // Keys of row `row`: the first n_sel entries of its index list, or (DENSE) every
 // valid position 0 .. n-1 in order, n = its sequence length (causal: up to its
@@ -204,12 +194,10 @@ __device__ __forceinline__ void split_merge(const AttnArgs &a, int row, int g, i
     }
 }
 
-// MQK: matrix-core logits and weighted V with per-wave softmax states.  NW:
-// waves per workgroup (4; 1 in the many-unit form).
-template <int G, bool PAGED, bool DENSE, bool MQK, int NW>
+// NW: waves per workgroup (4; 1 in the many-unit form).
+template <int G, bool PAGED, bool DENSE, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW < 4 && G <= 5 ? 5 : 1)))
 void sparse_attn_kernel(AttnArgs a) {
-    static_assert(NW == 4 || MQK, "fewer waves per workgroup: the matrix-core form only");
     constexpr int CH = 16 * NW;  // tokens per chunk: 16 per wave
     // Many-unit form (NW < 4): one wave per workgroup and five waves per
     // SIMD (G <= 5; G = 8 needs 97 registers and 10.6 KB of LDS, so four), so
@@ -220,15 +208,10 @@ void sparse_attn_kernel(AttnArgs a) {
     // needed.
     constexpr bool QLDS = NW < 4;
     __shared__ __align__(16) u32x4 s_qb[QLDS ? G : 1][QLDS ? 16 : 1];  // [head][16-byte piece]
-    constexpr int NV = pow2_at_least(4 * G);   // logits per lane before the reduction
-    constexpr int NO = pow2_at_least(8 * G);   // accumulators per lane before the reduction
-    __shared__ float zs[G][64];                // logits -> weights of the current chunk
-    __shared__ float s_scale[G];               // per-head rescale factor of this chunk
-    __shared__ float s_ml[G][2];               // running max (log2 domain) and denominator
     __shared__ __align__(16) float red[NW][G * kHeadDim];  // cross-wave reduction of the accumulators
-    // MQK: per wave, its 16 gathered K rows (16 x 16 pieces of 16 bytes, padded)
-    __shared__ __align__(16) u32x4 s_kt[MQK ? NW : 1][MQK ? 16 : 1][MQK ? kKtPitch : 1];
-    __shared__ float s_wml[MQK ? NW : 1][G][2];  // MQK: each wave's (max, sum) per head
+    // per wave, its 16 gathered K rows (16 x 16 pieces of 16 bytes, padded)
+    __shared__ __align__(16) u32x4 s_kt[NW][16][kKtPitch];
+    __shared__ float s_wml[NW][G][2];  // each wave's (max, sum) per head
 
     // flattened grid, few (row, KV head) units: (row * kv_heads + g) * splits + split;
     // many units (kManyUnits or more): split * units + (row * kv_heads + g), so that
@@ -298,14 +281,8 @@ void sparse_attn_kernel(AttnArgs a) {
                             : sel_at(sel, min(tok_begin + cfirst * CH + i * 4 * NW + wave * 4 + qq, a.top_k - 1));
     }
 
-    uint4 qv[MQK ? 1 : G];
-    bf16x8 qb[4];  // MQK: B operands, Q^T (32 dims x 16 head columns, heads >= G zero)
-    if (!MQK) {
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-            qv[h] = *reinterpret_cast<const uint4 *>(
-                a.q + ((size_t)row * Hq + g * G + h) * kHeadDim + sub * 8);
-    } else {
+    bf16x8 qb[4];  // B operands, Q^T (32 dims x 16 head columns, heads >= G zero)
+    {
         const int hq = min(sub, G - 1);
         const uint16_t *qp = a.q + ((size_t)row * Hq + g * G + hq) * kHeadDim + qq * 8;
 #pragma unroll
@@ -318,20 +295,11 @@ void sparse_attn_kernel(AttnArgs a) {
             }
         }
     }
-    if (tid < G) {
-        s_ml[tid][0] = -INFINITY;
-        s_ml[tid][1] = 0.0f;
-    }
-    float acc[G][8];
+    float m_run = -INFINITY, l_run = 0.0f;  // head sub's running max / sum (this wave)
+    // weighted V per 16-dim block blk, lane (qq, sub): heads 4qq + r, dim 8sub + blk
+    f32x4 pacc[8];
 #pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int d = 0; d < 8; ++d) acc[h][d] = 0.0f;
-    float m_run = -INFINITY, l_run = 0.0f;  // MQK: head sub's running max / sum (this wave)
-    // MQK: weighted V per 16-dim block blk, lane (qq, sub): heads 4qq + r, dim 8sub + blk
-    f32x4 pacc[MQK ? 8 : 1];
-#pragma unroll
-    for (int i = 0; i < (MQK ? 8 : 1); ++i) pacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 8; ++i) pacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     for (int ci = 0, c = cfirst, c0 = tok_begin; ROT ? ci < nch : c0 < tok_end; ++ci, c0 += CH) {
         int c0_next = c0 + CH;
@@ -382,37 +350,7 @@ void sparse_attn_kernel(AttnArgs a) {
         // this the scheduler sinks the V loads below the logits, which costs a
         // second memory round trip per chunk).
         __builtin_amdgcn_sched_barrier(0);
-        // weight x V with the lane's tokens in pairs (rounds 0, 1 and 2, 3): bf16
-        // weights and values into v_dot2_f32_bf16, fp32 accumulation.  weight(h, i):
-        // the weight of head h for this lane's round-i token (0 past the end).
-        auto weighted_v = [&](auto weight) {
-#pragma unroll
-            for (int pr = 0; pr < 2; ++pr) {
-                bf16x2 wp[G];
-#pragma unroll
-                for (int h = 0; h < G; ++h)
-                    wp[h] = bf16x2{(__bf16)weight(h, 2 * pr), (__bf16)weight(h, 2 * pr + 1)};
-                const uint32_t va[4] = {vr[2 * pr].x, vr[2 * pr].y, vr[2 * pr].z, vr[2 * pr].w};
-                const uint32_t vb[4] = {vr[2 * pr + 1].x, vr[2 * pr + 1].y, vr[2 * pr + 1].z,
-                                        vr[2 * pr + 1].w};
-#pragma unroll
-                for (int c2 = 0; c2 < 4; ++c2) {
-                    // dims 2c2 and 2c2+1 of both tokens: {va.lo, vb.lo} and {va.hi, vb.hi}
-                    const bf16x2 lo = __builtin_bit_cast(
-                        bf16x2, __builtin_amdgcn_perm(vb[c2], va[c2], 0x05040100u));
-                    const bf16x2 hi = __builtin_bit_cast(
-                        bf16x2, __builtin_amdgcn_perm(vb[c2], va[c2], 0x07060302u));
-#pragma unroll
-                    for (int h = 0; h < G; ++h) {
-                        acc[h][2 * c2] =
-                            __builtin_amdgcn_fdot2_f32_bf16(wp[h], lo, acc[h][2 * c2], false);
-                        acc[h][2 * c2 + 1] =
-                            __builtin_amdgcn_fdot2_f32_bf16(wp[h], hi, acc[h][2 * c2 + 1], false);
-                    }
-                }
-            }
-        };
-        if (MQK) {
+        {
             // Logits on the matrix cores: C = K_w (16 tokens x 128) x Q^T (128 x 16
             // head columns).  The wave's 16 K rows (gathered as above: token slot
             // r = 4i + qq is chunk token 4 NW i + 4w + qq) go through this wave's LDS
@@ -495,60 +433,10 @@ void sparse_attn_kernel(AttnArgs a) {
                 pacc[2 * c2 + 1] =
                     __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, bhi, pacc[2 * c2 + 1], 0, 0, 0);
             }
-        } else {
-            // logits: value index i*G + h, transpose-reduced over the 16 lanes of the quarter
-            float p[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) p[v] = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int h = 0; h < G; ++h) p[i * G + h] = dot8_bf16(kr[i], qv[h], 0.0f);
-            transpose_reduce<NV, 8, 1, NV>(p, sub);
-            // lane `sub` now holds value indices [sub*NV/16, sub*NV/16 + NV/16) (NV >= 16)
-            // or index sub / (16/NV) (NV < 16).
-            constexpr int PER = NV >= 16 ? NV / 16 : 1;
-#pragma unroll
-            for (int v = 0; v < PER; ++v) {
-                const int orig = NV >= 16 ? sub * PER + v : sub / (16 / NV);
-                if (orig < 4 * G) {
-                    const int i = orig / G, h = orig - i * G;
-                    const int tl = i * 16 + wave * 4 + qq;
-                    zs[h][tl] = c0 + tl < tok_end ? p[v] * a.scale_log2 : -INFINITY;
-                }
-            }
-        }
-        if (!MQK) {
-        __syncthreads();
-        // per-head chunk statistics and online-softmax update
-        for (int h = wave; h < G; h += 4) {
-            const float z = zs[h][lane];
-            const float mx = wave_max(z);
-            const float m_old = s_ml[h][0];
-            const float m_new = fmaxf(m_old, mx);   // finite: the chunk has a valid token
-            const float w = exp2f(z - m_new);        // z = -inf -> 0
-            const float sum = wave_sum(w);
-            zs[h][lane] = w;
-            if (lane == 0) {
-                const float sc = exp2f(m_old - m_new);  // m_old = -inf -> 0
-                s_scale[h] = sc;
-                s_ml[h][0] = m_new;
-                s_ml[h][1] = s_ml[h][1] * sc + sum;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            const float sc = s_scale[h];
-#pragma unroll
-            for (int d = 0; d < 8; ++d) acc[h][d] *= sc;
-        }
-        weighted_v([&](int h, int i) { return zs[h][i * 16 + wave * 4 + qq]; });
-        __syncthreads();  // zs / s_scale are rewritten by the next chunk
         }
     }
 
-    if constexpr (MQK) {
+    {
         // the wave's weighted V is complete in the C tiles: head 4qq + r, dims 8sub..8sub+7
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -560,55 +448,30 @@ void sparse_attn_kernel(AttnArgs a) {
                     make_float4(pacc[4][r], pacc[5][r], pacc[6][r], pacc[7][r]);
             }
         }
-    } else {
-    // ---- reduce the accumulators over the 4 quarters of each wave (lanes ^16, ^32) ----
-    float o[NO];
-#pragma unroll
-    for (int v = 0; v < NO; ++v) o[v] = 0.0f;
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int d = 0; d < 8; ++d) o[h * 8 + d] = acc[h][d];
-    transpose_reduce<NO, 32, 16, NO>(o, lane);
-    // lane (qq, sub) holds value indices [qq*NO/4, qq*NO/4 + NO/4); index = h*8 + d
-#pragma unroll
-    for (int v = 0; v < NO / 4; ++v) {
-        const int orig = qq * (NO / 4) + v;
-        if (orig < 8 * G) {
-            const int h = orig >> 3, d = orig & 7;
-            red[wave][h * kHeadDim + sub * 8 + d] = o[v];
-        }
     }
-    }
-    if (MQK && qq == 0 && sub < G) {  // this wave's (max, sum) of head sub
+    if (qq == 0 && sub < G) {  // this wave's (max, sum) of head sub
         s_wml[wave][sub][0] = m_run;
         s_wml[wave][sub][1] = l_run;
     }
     __syncthreads();
-    // (max, sum, weighted V) of head h over the workgroup: with per-wave softmax
-    // states (MQK) the NW waves combine by the log-sum-exp rule
+    // (max, sum, weighted V) of head h over the workgroup: the NW waves' softmax
+    // states combine by the log-sum-exp rule
     auto combine = [&](int h, int e, float &m, float &l, float &sum) {
-        if constexpr (MQK) {
-            if constexpr (NW == 4) {
-                m = fmaxf(fmaxf(s_wml[0][h][0], s_wml[1][h][0]), fmaxf(s_wml[2][h][0], s_wml[3][h][0]));
-            } else {
-                m = s_wml[0][h][0];
-#pragma unroll
-                for (int w4 = 1; w4 < NW; ++w4) m = fmaxf(m, s_wml[w4][h][0]);
-            }
-            l = 0.0f;
-            sum = 0.0f;
-#pragma unroll
-            for (int w4 = 0; w4 < NW; ++w4) {
-                const float mw = s_wml[w4][h][0];
-                const float f = mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - m);
-                l = fmaf(f, s_wml[w4][h][1], l);
-                sum = fmaf(f, red[w4][e], sum);
-            }
+        if constexpr (NW == 4) {
+            m = fmaxf(fmaxf(s_wml[0][h][0], s_wml[1][h][0]), fmaxf(s_wml[2][h][0], s_wml[3][h][0]));
         } else {
-            m = s_ml[h][0];
-            l = s_ml[h][1];
-            sum = red[0][e] + red[1][e] + red[2][e] + red[3][e];
+            m = s_wml[0][h][0];
+#pragma unroll
+            for (int w4 = 1; w4 < NW; ++w4) m = fmaxf(m, s_wml[w4][h][0]);
+        }
+        l = 0.0f;
+        sum = 0.0f;
+#pragma unroll
+        for (int w4 = 0; w4 < NW; ++w4) {
+            const float mw = s_wml[w4][h][0];
+            const float f = mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - m);
+            l = fmaf(f, s_wml[w4][h][1], l);
+            sum = fmaf(f, red[w4][e], sum);
         }
     };
     // one split, or (with the in-kernel merge) the only split that holds tokens
@@ -751,15 +614,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     }
 }
 
-// Splits per (row, KV head).  Sparse attention on contiguous caches (the
-// matrix-core form) aims at about 256 workgroups (one per CU) with at most 8
-// chunks of 64 tokens per split; everything else at about 1024 (four per CU).
-// Either way a split keeps at least four chunks while that still leaves 256
+// Splits per (row, KV head).  Sparse attention aims at about 256 workgroups (one
+// per CU) with at most 8 chunks of 64 tokens per split (on paged caches never at
+// more splits than 1024 workgroups give); dense attention at about 1024 (four per
+// CU).  Either way a split keeps at least four chunks while that still leaves 256
 // workgroups, so that the per-workgroup prologue and final merge are spread
-// over more chunks.  Measured with the matrix-core form: 128K, 8 splits of 4
-// chunks against 16 of 2 and 32 of 1; 32K, 4 splits of 8 chunks against 8 of 4.
-// The paged 32-sequence ragged batch keeps 4 splits of 8 chunks (1 split is
-// far slower there) and the 4K single-sequence step one chunk per split.  With
+// over more chunks.  Measured: 128K, 8 splits of 4 chunks against 16 of 2 and 32
+// of 1; 32K, 4 splits of 8 chunks against 8 of 4; paged, 16 x 8000 tokens (k =
+// 2048, 8 layers) 4 splits of 8 chunks 227 us against 242 for 8 of 4, 32 x 3000 (k
+// = 512) 1 of 8 131 against 143 for 2 of 4.  The 4K single-sequence step takes one
+// chunk per split.  With
 // many units (chunked prefill: thousands of rows) the grid is far wider than
 // the chip anyway; there each list is cut into kManySplits stretches, issued
 // stretch by stretch over all rows, so that the K/V rows gathered at any time
@@ -773,9 +637,13 @@ static void plan_splits(const Geometry &g, int keys, bool dense, int &splits,
                         int &chunks_per_split) {
     const int chunks = div_up(keys, 64);
     const long units = (long)g.rows * g.kv_heads;
-    const bool wide = !dense && g.page_shift < 0;  // matrix-core form: fewer, longer workgroups
-    long want = units > 0 ? ((wide ? 256 : 1024) + units - 1) / units : 1;
-    if (wide && want < (chunks + 7) / 8) want = (chunks + 7) / 8;  // at most 8 chunks per split
+    const long finest = units > 0 ? (1024 + units - 1) / units : 1;
+    long want = finest;
+    if (!dense) {
+        want = units > 0 ? (256 + units - 1) / units : 1;
+        if (want < (chunks + 7) / 8) want = (chunks + 7) / 8;  // at most 8 chunks per split
+        if (g.page_shift >= 0 && want > finest) want = finest;
+    }
     if (units >= kManyUnits && want < kManySplits) want = kManySplits;
     const long cap = units * (chunks / 4) >= 256 ? chunks / 4 : chunks;
     if (want > cap) want = cap;
@@ -821,15 +689,12 @@ static hipError_t launch_merge(const AttnArgs &a, int units, hipStream_t stream)
 template <int G, bool DENSE>
 static hipError_t launch_attn_g(const AttnArgs &a, bool paged, dim3 grid, int units,
                                 hipStream_t stream, hipEvent_t split_done) {
-    // Logits on the matrix cores with per-wave softmax states for contiguous
-    // caches and for many units (chunked prefill); paged decode grids keep the
-    // vector-unit logits and the shared softmax, which measured faster there.
     const bool many = grid.x / a.splits >= (unsigned)kManyUnits;
     constexpr int NWM = kManyUnitWaves;
-    if (paged && many) sparse_attn_kernel<G, true, DENSE, true, NWM><<<grid, dim3(64 * NWM), 0, stream>>>(a);
-    else if (paged) sparse_attn_kernel<G, true, DENSE, false, 4><<<grid, dim3(256), 0, stream>>>(a);
-    else if (many) sparse_attn_kernel<G, false, DENSE, true, NWM><<<grid, dim3(64 * NWM), 0, stream>>>(a);
-    else sparse_attn_kernel<G, false, DENSE, true, 4><<<grid, dim3(256), 0, stream>>>(a);
+    if (paged && many) sparse_attn_kernel<G, true, DENSE, NWM><<<grid, dim3(64 * NWM), 0, stream>>>(a);
+    else if (paged) sparse_attn_kernel<G, true, DENSE, 4><<<grid, dim3(256), 0, stream>>>(a);
+    else if (many) sparse_attn_kernel<G, false, DENSE, NWM><<<grid, dim3(64 * NWM), 0, stream>>>(a);
+    else sparse_attn_kernel<G, false, DENSE, 4><<<grid, dim3(256), 0, stream>>>(a);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && split_done) e = hipEventRecord(split_done, stream);
     if (e != hipSuccess || a.splits == 1 || a.tickets) return e;
