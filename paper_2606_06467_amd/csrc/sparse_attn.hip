@@ -633,13 +633,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // workgroups gather from about one chunk's share of it, with one wave per
 // workgroup so that many rows are resident.  keys: the
 // most keys a row can have (top_k, or max_len for dense attention).
+// sizing: the plan that the partial buffer is sized for, which on paged caches is
+// the finer one (workspace sizes, and the steps that a fixed scratch refuses, do
+// not depend on which of the two is run).
 static void plan_splits(const Geometry &g, int keys, bool dense, int &splits,
-                        int &chunks_per_split) {
+                        int &chunks_per_split, bool sizing = false) {
     const int chunks = div_up(keys, 64);
     const long units = (long)g.rows * g.kv_heads;
     const long finest = units > 0 ? (1024 + units - 1) / units : 1;
     long want = finest;
-    if (!dense) {
+    if (!dense && !(sizing && g.page_shift >= 0)) {
         want = units > 0 ? (256 + units - 1) / units : 1;
         if (want < (chunks + 7) / 8) want = (chunks + 7) / 8;  // at most 8 chunks per split
         if (g.page_shift >= 0 && want > finest) want = finest;
@@ -655,7 +658,7 @@ static void plan_splits(const Geometry &g, int keys, bool dense, int &splits,
 
 size_t attn_partial_floats(const Geometry &g, bool dense) {
     int splits, cps;
-    plan_splits(g, dense ? g.max_len : g.top_k, dense, splits, cps);
+    plan_splits(g, dense ? g.max_len : g.top_k, dense, splits, cps, true);
     if (splits == 1) return 0;
     return (size_t)g.rows * g.q_heads * splits * (kHeadDim + 2);
 }

@@ -38,6 +38,8 @@
 
 namespace clsa {
 
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // any float address
+
 // Refinement digits below the coarse one: bits 20..10, then 9..0.
 constexpr int kMidShift = 10;
 constexpr int kMidBins = 1 << (kCoarseShift - kMidShift);  // 2048
@@ -592,10 +594,22 @@ __global__ __launch_bounds__(NT) void topk_short_kernel(TopkRowArgs a) {
     const int tid = threadIdx.x;
     const float *srow = a.scores + (size_t)row * a.max_len;
     const int p0 = tid * kShortKeys;
-    // loads issued before the row's length is known (clamped to its capacity)
+    // loads issued before the row's length is known (clamped to its capacity):
+    // four of 16 bytes, whatever the row's alignment (16 of 4 bytes, a line per
+    // lane each: 16384 keys 36.5 us of a two-layer step, now 32.0; 4096 keys 33.8
+    // of the four-layer step, now 32.5); one by one in the row's last thread
     uint32_t key[kShortKeys];
+    if (p0 + kShortKeys <= a.max_len) {
 #pragma unroll
-    for (int j = 0; j < kShortKeys; ++j) key[j] = score_key(srow[min(p0 + j, a.max_len - 1)]);
+        for (int j = 0; j < kShortKeys; j += 4) {
+            const f32x4u v = *reinterpret_cast<const f32x4u *>(srow + p0 + j);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) key[j + c] = score_key(v[c]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kShortKeys; ++j) key[j] = score_key(srow[min(p0 + j, a.max_len - 1)]);
+    }
     const int b = row / a.n_q;
     const int n = valid_keys(a.seq_lens, a.q_pos, a.causal, b, row, a.max_len);
     const int k = a.top_k;
