@@ -110,7 +110,11 @@ __global__ __launch_bounds__(512) void project_splitk_kernel(ProjArgs a) {
 
 // Many rows: the tiled product.
 constexpr int kGemmM = 128, kGemmN = 128, kGemmK = 64;
-constexpr int kGemmPitch = kGemmK + 8;       // bf16 per staged row (16 bytes of padding)
+// A staged row is 8 pieces of 16 bytes; piece p of row r lies at p ^ ((r >> 1) & 7):
+// the 16 rows of an operand read and the two rows of a store then fall on all 64
+// banks once (rows padded by 16 bytes: a third of the LDS cycles were conflicts of
+// the stores).
+constexpr int kGemmPitch = kGemmK;           // bf16 per staged row
 constexpr int kGemmOutPitch = kGemmN + 8;    // bf16 per staged output row
 constexpr size_t kGemmLds = sizeof(uint16_t) * 2 * 2 * kGemmM * kGemmPitch;
 
@@ -144,6 +148,7 @@ __global__ __launch_bounds__(256, 2) void project_gemm_kernel(ProjArgs a) {
     // staging: thread t moves 16-byte pieces t + 256 i (i < 4) of each 128 x 64
     // tile: row (t >> 3) + 32 i, columns 8 (t & 7) .. + 8
     const int lrow = tid >> 3, lcol = (tid & 7) * 8;
+    const int wcol = ((tid & 7) ^ ((lrow >> 1) & 7)) * 8, rswz = (col >> 1) & 7;
     const uint16_t *hp[4], *wp[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -166,8 +171,8 @@ __global__ __launch_bounds__(256, 2) void project_gemm_kernel(ProjArgs a) {
     auto lstore = [&](int set, int st) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            *reinterpret_cast<u32x4 *>(&s_ab[st][0][lrow + 32 * i][lcol]) = ra[set][i];
-            *reinterpret_cast<u32x4 *>(&s_ab[st][1][lrow + 32 * i][lcol]) = rb[set][i];
+            *reinterpret_cast<u32x4 *>(&s_ab[st][0][lrow + 32 * i][wcol]) = ra[set][i];
+            *reinterpret_cast<u32x4 *>(&s_ab[st][1][lrow + 32 * i][wcol]) = rb[set][i];
         }
     };
     f32x4 c[4][4];
@@ -185,23 +190,39 @@ __global__ __launch_bounds__(256, 2) void project_gemm_kernel(ProjArgs a) {
         const int k = kt + h;
         const int st = h;
         gload(h, min(k + 2, nk - 1) * kGemmK);  // unconditional (the last steps reload a valid step, never stored): a static load count
+        // operand o of 32-wide half ks: A rows (o < 4) and B features of the wave's quadrant
+        bf16x8 op[2][8];
+        auto read_op = [&](int ks, int o) {
+            const int r = (o < 4 ? wm * 64 + o * 16 : wn * 64 + (o - 4) * 16) + col;
+            op[ks][o] = __builtin_bit_cast(
+                bf16x8, *reinterpret_cast<const u32x4 *>(&s_ab[st][o >> 2][r][((ks * 4 + grp) ^ rswz) * 8]));
+        };
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ks = 0; ks < kGemmK / 32; ++ks) {
-            bf16x8 av[4], bv[4];
+        for (int o = 0; o < 8; ++o) read_op(0, o < 4 ? o + 4 : o - 4);
+        // 16 parts of two products whose order is pinned: the first eight each read
+        // an operand of the second half, the others each store a piece of the next
+        // step (the last step stores an old piece that is not read).  8192 rows x 2560
+        // features x 2560: 127.6 us with padded rows and the compiler's order, 124.0
+        // swizzled, 117.4 in this order; 32-wide steps (three workgroups per CU) 139.6.
+        // What bounds it now: 640 tiles on 512 resident workgroups, and the step's
+        // own chain of barrier, operand reads and products at two waves per SIMD.
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                av[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(
-                                                       &s_ab[st][0][wm * 64 + t * 16 + col][ks * 32 + grp * 8]));
-                bv[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(
-                                                       &s_ab[st][1][wn * 64 + t * 16 + col][ks * 32 + grp * 8]));
+        for (int p = 0; p < 16; ++p) {
+            const int ks = p >> 3;
+            if (ks == 0) read_op(1, p < 4 ? p + 4 : p - 4);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int m = 2 * (p & 7) + e, mt = m >> 2, nt = m & 3;
+                c[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[ks][mt], op[ks][4 + nt], c[mt][nt], 0, 0, 0);
             }
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-                    c[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv[nt], c[mt][nt], 0, 0, 0);
+            if (ks == 1) {
+                const int i = (p & 7) >> 1;
+                if (p & 1) *reinterpret_cast<u32x4 *>(&s_ab[st ^ 1][1][lrow + 32 * i][wcol]) = rb[h ^ 1][i];
+                else *reinterpret_cast<u32x4 *>(&s_ab[st ^ 1][0][lrow + 32 * i][wcol]) = ra[h ^ 1][i];
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (k + 1 < nk) lstore(h ^ 1, h ^ 1);
         __syncthreads();
       }
     }
