@@ -13,10 +13,12 @@
 // 4 * (l >> 4) + r (r = 0..3) of feature (l & 15).  A wave owns 16 rows x 64
 // features (four feature tiles).
 //   * few rows (decode): a workgroup of 8 waves splits d_model eight ways for
-//     one 16-row x 16-feature tile, each wave issuing all of its loads before
-//     its first product, and the eight partial tiles are added in LDS: the
-//     weights (13 MB at d_model 2560, the bytes that bound this case) are then
-//     read by 160 workgroups at once;
+//     one tile of 16 or 32 rows x 16 features, each wave issuing all of its loads
+//     before its first product (in two batches past d_model 3072), and the eight
+//     partial tiles are added in LDS: the weights (13 MB at d_model 2560, the
+//     bytes that bound this case) are then read by 160 workgroups at once.
+//     Models wider than 3072 had gone to the tiled product, 20 workgroups that
+//     walk d_model alone: 16 rows, d_model 4096 37 us, now 10; 8192 70, now 17;
 //   * many rows (prefill): a tiled product, 128 rows x 128 features per
 //     workgroup of 4 waves (64 x 64 each, 4 x 4 tiles of 16 x 16), d_model in
 //     steps of 64 staged through LDS (double-buffered: the next step's global
@@ -32,7 +34,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitWaves = 8;     // d_model split of the few-rows kernel
-constexpr int kSplitMaxD = 3072;   // largest d_model of the few-rows kernel (register budget)
+// Rows up to which the weights' bytes bound the product.  Against the tiled
+// product (2560 features): 96 rows, d_model 2560 15.8 us against 28.4; 128 rows 22.2
+// against 30.1, d_model 4096 33.9 against 42.6; 192 rows, 4096 44.7 against 41.5.
+constexpr int kSplitMaxRows = 128;
 
 struct ProjArgs {
     const uint16_t *h;         // [rows, d]
@@ -75,36 +80,51 @@ __device__ __forceinline__ void store_feature(const ProjArgs &a, int r, int f, f
     else a.v_cache[row * a.kvw + (f - 512 - a.kvw)] = bits;
 }
 
-// Few rows: one 16-row x 16-feature tile per workgroup, d_model split over 8
-// waves of KS 32-dim steps each (d_model = 256 * KS).
-template <int KS, bool PAGED>
+// Few rows: one 16 RT-row x 16-feature tile per workgroup, d_model split over 8
+// waves of NB * KS 32-dim steps each (d_model = 256 * NB * KS), KS at a time.
+// RT = 2: a weight is read once for 32 rows (launch_splitk: when).
+template <int KS, int NB, int RT, bool PAGED>
 __global__ __launch_bounds__(512) void project_splitk_kernel(ProjArgs a) {
-    __shared__ float part[kSplitWaves][16][16 + 1];
+    __shared__ float part[kSplitWaves][16 * RT][16 + 1];
     const int ft = blockIdx.x, rt = blockIdx.y;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int col = lane & 15, grp = lane >> 4;
-    const int k0 = wave * KS * 32 + grp * 8;
-    const uint16_t *hp = a.h + (size_t)min(rt * 16 + col, a.rows - 1) * a.d + k0;
+    const int k0 = wave * NB * KS * 32 + grp * 8;
+    const uint16_t *hp[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+        hp[t] = a.h + (size_t)min((rt * RT + t) * 16 + col, a.rows - 1) * a.d + k0;
     const uint16_t *wp = a.w + (size_t)(ft * 16 + col) * a.d + k0;
-    bf16x8 av[KS], bv[KS];
+    f32x4 c[RT];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        av[s] = ld8(hp + s * 32);
-        bv[s] = ld8(wp + s * 32);
+    for (int t = 0; t < RT; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        bf16x8 av[RT][KS], bv[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            bv[s] = ld8(wp + (nb * KS + s) * 32);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) av[t][s] = ld8(hp[t] + (nb * KS + s) * 32);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // every load in flight before the first product
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+                c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t][s], bv[s], c[t], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);  // every load in flight before the first product
-    f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < KS; ++s) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[s], bv[s], c, 0, 0, 0);
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) part[wave][4 * grp + r][col] = c[r];
+        for (int r = 0; r < 4; ++r) part[wave][16 * t + 4 * grp + r][col] = c[t][r];
     __syncthreads();
-    if (threadIdx.x < 256) {  // 16 x 16 outputs
+    if (threadIdx.x < 256 * RT) {  // 16 RT x 16 outputs
         const int rr = threadIdx.x >> 4, f = threadIdx.x & 15;
         float sum = 0.0f;
 #pragma unroll
         for (int w = 0; w < kSplitWaves; ++w) sum += part[w][rr][f];
-        store_feature<PAGED>(a, rt * 16 + rr, ft * 16 + f, sum);
+        store_feature<PAGED>(a, rt * 16 * RT + rr, ft * 16 + f, sum);
     }
 }
 
@@ -273,10 +293,19 @@ bool project_supported(int d_model) {
     return d_model >= 512 && d_model <= 8192 && d_model % 512 == 0;
 }
 
-template <int KS>
-static void launch_splitk(const ProjArgs &a, bool paged, dim3 grid, hipStream_t stream) {
-    if (paged) project_splitk_kernel<KS, true><<<grid, dim3(512), 0, stream>>>(a);
-    else project_splitk_kernel<KS, false><<<grid, dim3(512), 0, stream>>>(a);
+template <int KS, int NB = 1>
+static void launch_splitk(const ProjArgs &a, bool paged, int n_feat, hipStream_t stream) {
+    // 32 rows a workgroup where 16 would not fit the chip in one round but 32 do
+    // (32 rows x 2560 features, d_model 2560: 9.1 us against 11.3; 4096: 13.2 against
+    // 16.5), and from 65 rows on; 32 rows x 1536 features fit with 16 (9.3 against 12.8
+    // at 4096), 48 x 2560 fit with neither (11.3 against 13.9)
+    const int tiles = n_feat / 16;
+    const bool two = tiles * div_up(a.rows, 16) > 256 && (tiles * div_up(a.rows, 32) <= 256 || a.rows > 64);
+    const dim3 grid(tiles, div_up(a.rows, two ? 32 : 16)), block(512);
+    if (two && paged) project_splitk_kernel<KS, NB, 2, true><<<grid, block, 0, stream>>>(a);
+    else if (two) project_splitk_kernel<KS, NB, 2, false><<<grid, block, 0, stream>>>(a);
+    else if (paged) project_splitk_kernel<KS, NB, 1, true><<<grid, block, 0, stream>>>(a);
+    else project_splitk_kernel<KS, NB, 1, false><<<grid, block, 0, stream>>>(a);
 }
 
 hipError_t launch_project(const Geometry &g, int d_model, const void *h, const void *w,
@@ -302,15 +331,25 @@ hipError_t launch_project(const Geometry &g, int d_model, const void *h, const v
     if (g.rows == 0) return hipSuccess;
     const int n_feat = 512 + 2 * a.kvw;  // a multiple of 256 (kv_heads * 128 per K and V)
     const bool paged = g.page_shift >= 0;
-    if (g.rows <= 64 && d_model <= kSplitMaxD) {
-        const dim3 grid(n_feat / 16, div_up(g.rows, 16));
+    if (g.rows <= kSplitMaxRows) {
         switch (d_model / 512) {
-            case 1: launch_splitk<2>(a, paged, grid, stream); break;
-            case 2: launch_splitk<4>(a, paged, grid, stream); break;
-            case 3: launch_splitk<6>(a, paged, grid, stream); break;
-            case 4: launch_splitk<8>(a, paged, grid, stream); break;
-            case 5: launch_splitk<10>(a, paged, grid, stream); break;
-            case 6: launch_splitk<12>(a, paged, grid, stream); break;
+            case 1: launch_splitk<2>(a, paged, n_feat, stream); break;
+            case 2: launch_splitk<4>(a, paged, n_feat, stream); break;
+            case 3: launch_splitk<6>(a, paged, n_feat, stream); break;
+            case 4: launch_splitk<8>(a, paged, n_feat, stream); break;
+            case 5: launch_splitk<10>(a, paged, n_feat, stream); break;
+            case 6: launch_splitk<12>(a, paged, n_feat, stream); break;
+            // past 3072 (96 operand registers) in two batches
+            case 7: launch_splitk<7, 2>(a, paged, n_feat, stream); break;
+            case 8: launch_splitk<8, 2>(a, paged, n_feat, stream); break;
+            case 9: launch_splitk<9, 2>(a, paged, n_feat, stream); break;
+            case 10: launch_splitk<10, 2>(a, paged, n_feat, stream); break;
+            case 11: launch_splitk<11, 2>(a, paged, n_feat, stream); break;
+            case 12: launch_splitk<12, 2>(a, paged, n_feat, stream); break;
+            case 13: launch_splitk<13, 2>(a, paged, n_feat, stream); break;
+            case 14: launch_splitk<14, 2>(a, paged, n_feat, stream); break;
+            case 15: launch_splitk<15, 2>(a, paged, n_feat, stream); break;
+            case 16: launch_splitk<16, 2>(a, paged, n_feat, stream); break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();

@@ -105,3 +105,16 @@ def test_many_rows_tiles_ragged_paged():
     pos[::50] = w.max_len
     pos[7] = -1
     _case(w, 2560, pos, 16, "600 rows, tiles + tail, paged")
+
+
+@pytest.mark.parametrize("rows,d_model,kvh,page", [
+    (16, 3584, 8, 0), (17, 2560, 8, 64), (33, 4096, 4, 0),      # 16 or 32 rows a workgroup
+    (48, 512, 8, 0), (64, 8192, 4, 0), (65, 3072, 8, 64),       # two batches past 3072
+    (128, 1536, 8, 0), (129, 5120, 4, 64)])                     # the last by the tiled product
+def test_few_rows_split_depth(rows, d_model, kvh, page):
+    """Edges of the few-rows form: rows per workgroup, and every kind of depth."""
+    w = inputs.small_workload(batch=1, lens=(400,), n_q=rows, n_layers=1, q_heads=4 * kvh,
+                              kv_heads=kvh, page_size=page, wid=106)
+    pos = [[(7 * r) % 400 for r in range(rows)]]
+    pos[0][rows // 2] = -1
+    _case(w, d_model, pos, 16, f"{rows} rows d={d_model} Hkv={kvh} page={page}")
