@@ -3,22 +3,18 @@
 //
 // Eq. 5: abar[b,t,j] = (1 / (L * Hq)) * sum over layers l and query heads h of
 // softmax_j(scale * q_l[b,t,h] . K[b,j,g(h)]) over the valid keys of row (b,t),
-// one shared key cache for every layer.  Logits on the matrix cores
-// (v_mfma_f32_16x16x32_bf16: A = 16 query rows x 32 dims, B = 32 dims x 16
-// keys; lane l supplies row / key (l & 15) for dims (l >> 4) * 8 .. +8 and
-// receives rows 4 * (l >> 4) + r of key (l & 15), so the 16 keys of one row
-// sit in one DPP row of 16 lanes):
-//   * kd_lse_kernel: per (64-row tile, layer, up to 4 heads of one KV head), an
-//     online softmax over the row's keys gives each row's log-sum-exp (log2
-//     units, in the workspace); each lane keeps statistics over its own keys
-//     and the 16 lanes of a row are combined once at the end.  When the caller
-//     already has these log-sum-exps (the dense forward pass of every layer
-//     makes them), kd_lse_import_kernel copies them in instead;
+// one shared key cache for every layer.  Logits on the bf16 matrix cores:
+//   * kd_lse_kernel: an online softmax over the row's keys gives each row's
+//     log-sum-exp (log2 units, in the workspace).  When the caller already has
+//     these log-sum-exps (the dense forward pass of every layer makes them),
+//     kd_lse_import_kernel copies them in instead;
 //   * kd_target_kernel: per (16-row, 64-key) tile, every (layer, head) adds
 //     exp(logit - lse) into the tile held in registers; the key operands of a
 //     KV head are loaded once for all layers and heads of its group, the four
 //     waves of a workgroup share their rows' query operands, and abar is
-//     written once, with no atomics.
+//     written once, with no atomics (v_mfma_f32_16x16x32_bf16: A = 16 query rows
+//     x 32 dims, B = 32 dims x 16 keys; lane l supplies row / key (l & 15) for
+//     dims (l >> 4) * 8 .. +8 and receives rows 4 * (l >> 4) + r of key (l & 15)).
 #include "clsa_internal.h"
 #include "device_common.h"
 
@@ -26,9 +22,9 @@ namespace clsa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr float kKdLog2e = 1.4426950408889634f;
-constexpr float kKdLn2 = 0.6931471805599453f;
 constexpr int kKdDim = 128;  // attention head dimension
 constexpr int kKdTile = 64;  // rows and keys per target tile
 
@@ -61,17 +57,6 @@ __device__ __forceinline__ void kd_row_limits(const KdArgs &a, int b, int t0, in
         n[r] = t < a.n_q ? valid_keys(a.seq_lens, a.q_pos, a.causal, b, b * a.n_q + t, a.max_len)
                          : 0;
     }
-}
-
-// A operands: query row t0 + col of layer l, head h (rows past n_q clamped).
-__device__ __forceinline__ void kd_load_query(const KdArgs &a, int b, int t0, int l, int h,
-                                              int col, int grp, bf16x8 (&qa)[4]) {
-    const int t = min(t0 + col, a.n_q - 1);
-    const uint16_t *p = a.q_layers +
-                        (((size_t)l * a.rows + (size_t)b * a.n_q + t) * a.q_heads + h) * kKdDim +
-                        grp * 8;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) qa[kb] = kd_ld8(p + kb * 32);
 }
 
 // B operands of keys j0 + 16 * ct + col of KV head g (keys past len clamped to
@@ -140,93 +125,84 @@ __device__ __forceinline__ float kd_max(float x, float y) {
     return __builtin_elementwise_maximum(x, y);
 }
 
-// Online softmax statistics of the lane's four rows over the lane's own four
-// keys of a tile, in log2 units: s is the sum of 2^(sl * z - base).  The base
-// follows the running maximum lazily: it moves only when a logit exceeds it by
-// more than 2^16 (then every row of the lane is rebased, on a branch the whole
-// wave takes), so that the steady state needs no rescaling exponential.  Terms
-// up to 2^16 keep the sums far from the fp32 range, and the relative precision
-// of the sum does not depend on the base.
-constexpr float kLazyMargin = 16.0f;
-
-template <bool FULL>
-__device__ __forceinline__ void kd_stats_update(const f32x4 (&c)[4], float sl, int j0, int col,
-                                                const int (&n)[4], float (&base)[4],
-                                                float (&s)[4]) {
-    float v[4][4], tm[4];
-    bool over = false;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-            v[r][ct] = FULL || j0 + 16 * ct + col < n[r] ? c[ct][r] : -INFINITY;
-        tm[r] = kd_max(kd_max(v[r][0], v[r][1]), kd_max(v[r][2], v[r][3])) * sl;
-        over |= tm[r] > base[r] + kLazyMargin;
-    }
-    if (__builtin_amdgcn_ballot_w64(over)) {  // rare: rebase every row of the wave
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float nb = kd_max(base[r], tm[r]);
-            if (nb != -INFINITY) {
-                s[r] *= kd_exp2(base[r] - nb);  // base = -inf: s is 0 anyway
-                base[r] = nb;
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const float b = base[r] == -INFINITY ? 0.0f : base[r];  // no key of the lane yet
-        s[r] += (kd_exp2(fmaf(v[r][0], sl, -b)) + kd_exp2(fmaf(v[r][1], sl, -b))) +
-                (kd_exp2(fmaf(v[r][2], sl, -b)) + kd_exp2(fmaf(v[r][3], sl, -b)));
-    }
-}
-
 constexpr int kStagePitch = kKdDim + 8;  // bf16 per staged row (272 bytes): the 16 rows read
                                          // by one 16-lane group fall on distinct banks
 
-// Log-sum-exp (log2 units) of every (layer, query head, row): a workgroup holds
-// 64 rows (16 per wave) and HP heads of one KV head, the query operands in
-// registers.  The key tiles of that KV head stream through LDS, double-buffered
-// and shared by the four waves (one barrier per tile); each key tile serves HP
-// heads.  grid: (((b * row_tiles + tile) * L + l) * (group / HP) + head block)
-// * kv_heads + g, so that the workgroups of one KV head land on the same XCD
-// when kv_heads divides 8.
-template <int HP, bool PAGED>
-__global__ __launch_bounds__(256) void kd_lse_kernel(KdArgs a) {
+constexpr int kLseWaves = 4;
+// Workgroups of the statistics pass from which a wave takes two items: two rounds
+// of the 512 such workgroups the chip holds.  Below, one item per wave fills it
+// better (32 / 8 heads, 1000 rows, 4 layers, 512 workgroups: 96 us with one, 103
+// with two; 8 / 8, 500 rows, 2 layers: 36 and 42); above, two share every key read
+// (16384 rows, 16 layers: 37.8 ms with one, 36.0 with two; about 1000 and 1500
+// workgroups measured the same either way).
+constexpr int kLseWide = 1024;
+
+// Log-sum-exp (log2 units) of every (layer, query head, row): a wave holds the
+// queries of IT (32-row block, query head) items of one KV head and layer in
+// registers (B of v_mfma_f32_32x32x16_bf16: lane l supplies column (l & 31) for
+// dims 8 * (l >> 5) .. + 8 and receives rows 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)
+// of that column), and the KV head's keys stream through LDS 64 at a time,
+// double-buffered and shared by the four waves (one barrier per tile); each key
+// operand serves every item.  The logits come transposed, 32 keys of one row per
+// lane, so a row's base and sum are one value per lane, the lanes' statistics are
+// combined once at the end, and the maximum of a tile is 16 three-operand maxima.
+// What bounds the pass is the vector work on the logits (it and the matrix
+// products hardly overlap on this chip): an fma, an exp2, an add and half a
+// maximum each.  The base follows the running maximum lazily: it moves only when a
+// logit exceeds it by more than 2^kLazyMargin (a branch the whole wave takes).
+// Measured, both passes of the target, against 16 rows x 16 keys per product with
+// four rows per lane (5.75 vector operations per logit): 16384 rows, 16 layers, 32
+// / 8 heads 35.2 ms against 37.4; 3000 rows, 8 layers, 20 / 4 heads 459 us against
+// 623; 500 rows, 2 layers, 32 / 8 heads 54 against 62.
+// grid: ((b * blocks + block of 4 * IT items) * L + l) * kv_heads + g, the last
+// rows first; the workgroups of one KV head land on the same XCD when kv_heads
+// divides 8.
+constexpr float kLazyMargin = 16.0f;
+template <int G, int IT, bool PAGED>  // G: query heads per KV head, IT: items per wave
+__global__ __launch_bounds__(64 * kLseWaves, 2) void kd_lse_kernel(KdArgs a) {
     __shared__ __align__(16) uint16_t s_k[2][kKdTile][kStagePitch];
-    __shared__ int s_nmax[4];
+    __shared__ int s_nmax[kLseWaves];
     int x = blockIdx.x;
     const int g = x % a.kv_heads;
     x /= a.kv_heads;
-    const int hsplit = a.group / HP;
-    const int hs = x % hsplit;
-    x /= hsplit;
     const int l = x % a.n_layers;
     x /= a.n_layers;
-    const int tile = x % a.row_tiles, b = x / a.row_tiles;
-    const int h0 = g * a.group + hs * HP;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col = lane & 15, grp = lane >> 4;
-    const int t0 = tile * kKdTile + wave * 16;
+    const int blk = a.row_tiles - 1 - x % a.row_tiles, b = x / a.row_tiles;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, hi = lane >> 5;
     const int len = clamp_len(a.seq_lens[b], a.max_len);
-    int n[4];
-    kd_row_limits(a, b, t0, grp, n);  // 0 for rows past n_q
-    const int nmax = kd_groups_max(max(max(n[0], n[1]), max(n[2], n[3])));
-    const int nmin = kd_groups_min(min(min(n[0], n[1]), min(n[2], n[3])));
-    if (lane == 0) s_nmax[wave] = nmax;
-    bf16x8 q[HP][4];
-    if (t0 < a.n_q) {
+    int t[IT], h[IT], n[IT], nmax = 0, nmin = a.max_len;
+    bf16x8 q[IT][8];
 #pragma unroll
-        for (int hh = 0; hh < HP; ++hh) kd_load_query(a, b, t0, l, h0 + hh, col, grp, q[hh]);
+    for (int i = 0; i < IT; ++i) {
+        const int item = (blk * kLseWaves + wave) * IT + i;
+        h[i] = g * G + item % G;
+        t[i] = item / G * 32 + col;
+        n[i] = t[i] < a.n_q
+                   ? valid_keys(a.seq_lens, a.q_pos, a.causal, b, b * a.n_q + t[i], a.max_len) : 0;
+        nmax = max(nmax, n[i]);
+        nmin = min(nmin, n[i]);
+        const uint16_t *p = a.q_layers +
+                            (((size_t)l * a.rows + (size_t)b * a.n_q + min(t[i], a.n_q - 1)) * a.q_heads +
+                             h[i]) * kKdDim + hi * 8;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) q[i][ks] = kd_ld8(p + 16 * ks);
     }
-    float m[HP][4], s[HP][4];  // per head and row: base (log2 units) and sum
 #pragma unroll
-    for (int hh = 0; hh < HP; ++hh)
+    for (int d = 1; d < 32; d <<= 1) {
+        nmax = max(nmax, __shfl_xor(nmax, d));
+        nmin = min(nmin, __shfl_xor(nmin, d));
+    }
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    nmin = __builtin_amdgcn_readfirstlane(nmin);
+    if (lane == 0) s_nmax[wave] = nmax;
+    float m[IT], s[IT];  // base (log2 units) and sum
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            m[hh][r] = -INFINITY;
-            s[hh][r] = 0.0f;
-        }
+    for (int i = 0; i < IT; ++i) {
+        m[i] = -INFINITY;
+        s[i] = 0.0f;
+    }
     __syncthreads();
     const int wg_max = max(max(s_nmax[0], s_nmax[1]), max(s_nmax[2], s_nmax[3]));
     const int tiles = div_up(wg_max, kKdTile);
@@ -261,39 +237,77 @@ __global__ __launch_bounds__(256) void kd_lse_kernel(KdArgs a) {
         if (u + 1 < tiles) fetch(u + 1, v);
         const int j0 = u * kKdTile;
         if (j0 < nmax) {  // uniform per wave
-            const int buf = u & 1;
-            bf16x8 kv[4][4];
+            f32x16 c[IT][2];  // [item][half of the tile]
 #pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
+            for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
-                    kv[ct][kb] = *reinterpret_cast<const bf16x8 *>(
-                        &s_k[buf][16 * ct + col][kb * 32 + grp * 8]);
-            const bool full = j0 + kKdTile <= nmin;
+                for (int i = 0; i < IT; ++i)
 #pragma unroll
-            for (int hh = 0; hh < HP; ++hh) {
-                f32x4 c[4];
-                kd_logits(q[hh], kv, c);
-                if (full) kd_stats_update<true>(c, a.scale_log2, j0, col, n, m[hh], s[hh]);
-                else kd_stats_update<false>(c, a.scale_log2, j0, col, n, m[hh], s[hh]);
+                    for (int r = 0; r < 16; ++r) c[i][kt][r] = 0.0f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) {
+                    const bf16x8 k = *reinterpret_cast<const bf16x8 *>(
+                        &s_k[u & 1][32 * kt + col][16 * ks + 8 * hi]);
+#pragma unroll
+                    for (int i = 0; i < IT; ++i)
+                        c[i][kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q[i][ks], c[i][kt], 0, 0, 0);
+                }
+            }
+            if (j0 + kKdTile > nmin) {  // uniform per wave
+#pragma unroll
+                for (int i = 0; i < IT; ++i)
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            c[i][kt][r] = j0 + 32 * kt + 8 * (r >> 2) + 4 * hi + (r & 3) < n[i] ? c[i][kt][r]
+                                                                                               : -INFINITY;
+            }
+            float mx[IT];
+            bool over = false;
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                float w = kd_max(c[i][0][0], c[i][1][0]);
+#pragma unroll
+                for (int r = 1; r < 16; ++r) w = kd_max(kd_max(w, c[i][0][r]), c[i][1][r]);
+                mx[i] = w * a.scale_log2;
+                over |= mx[i] > m[i] + kLazyMargin;
+            }
+            if (__builtin_amdgcn_ballot_w64(over)) {
+#pragma unroll
+                for (int i = 0; i < IT; ++i) {
+                    const float nb = kd_max(m[i], mx[i]);
+                    if (nb != -INFINITY) {
+                        s[i] *= kd_exp2(m[i] - nb);  // base = -inf: s is 0 anyway
+                        m[i] = nb;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const float base = m[i] == -INFINITY ? 0.0f : m[i];  // no key of the lane yet
+                float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[r & 3] += kd_exp2(fmaf(c[i][kt][r], a.scale_log2, -base));
+                s[i] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
             }
         }
         if (u + 1 < tiles) stage((u + 1) & 1, v);
         __syncthreads();
     }
-    if (t0 >= a.n_q) return;
 #pragma unroll
-    for (int hh = 0; hh < HP; ++hh)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float mr = row16_max(m[hh][r]);
-            const float part = m[hh][r] == -INFINITY ? 0.0f : s[hh][r] * exp2f(m[hh][r] - mr);
-            const float sr = row16_sum(part);
-            const int t = t0 + 4 * grp + r;
-            if (col == 0 && t < a.n_q)
-                a.lse2[((size_t)l * a.q_heads + h0 + hh) * a.rows_pad + (size_t)b * a.n_q + t] =
-                    n[r] > 0 ? mr + log2f(sr) : -INFINITY;
-        }
+    for (int i = 0; i < IT; ++i) {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m[i]), __float_as_uint(m[i]), false, false);
+        const float mr = kd_max(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        const float part = m[i] == -INFINITY ? s[i] : s[i] * exp2f(m[i] - mr);
+        r = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
+        const float sr = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        if (hi == 0 && t[i] < a.n_q)
+            a.lse2[((size_t)l * a.q_heads + h[i]) * a.rows_pad + (size_t)b * a.n_q + t[i]] =
+                n[i] > 0 ? mr + log2f(sr) : -INFINITY;
+    }
 }
 
 constexpr int kTgtChunk = 4;              // (layer, head) combinations per LDS stage
@@ -494,10 +508,12 @@ hipError_t launch_kd_target(const Geometry &g, int n_layers, const void *q_layer
     a.rows_pad = g.rows + 16;
     a.scale_log2 = g.softmax_scale * kKdLog2e;
     a.inv_lh = 1.0f / ((float)n_layers * (float)g.q_heads);
-    const long long tiles = (long long)g.batch * a.row_tiles;
-    // heads per workgroup of the statistics pass (a divisor of the group)
-    const int hp = g.group == 8 ? 4 : g.group;
-    const dim3 lse_grid((unsigned)(tiles * n_layers * (g.group / hp) * g.kv_heads));
+    // the statistics pass: blocks of 4 waves of `per_wave` (32 rows, query head)
+    // items per (KV head, layer)
+    const long long items = (long long)div_up(g.n_q, 32) * g.group;
+    const int per_wave = (items + 7) / 8 * g.batch * n_layers * g.kv_heads < kLseWide ? 1 : 2;
+    a.row_tiles = (int)((items + kLseWaves * per_wave - 1) / (kLseWaves * per_wave));
+    const dim3 lse_grid((unsigned)((long long)g.batch * a.row_tiles * n_layers * g.kv_heads));
     const bool paged = g.page_shift >= 0;
     if (lse_in) {  // the caller's log-sum-exps: no statistics pass
         const size_t total = (size_t)n_layers * g.rows * g.q_heads;
@@ -505,17 +521,20 @@ hipError_t launch_kd_target(const Geometry &g, int n_layers, const void *q_layer
         kd_lse_import_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0,
                                stream>>>(a, lse_in);
     } else {
-#define KD_LSE(HP)                                                              \
-    (paged ? kd_lse_kernel<HP, true><<<lse_grid, dim3(256), 0, stream>>>(a)    \
-           : kd_lse_kernel<HP, false><<<lse_grid, dim3(256), 0, stream>>>(a))
-        switch (hp) {
+#define KD_LSE_IT(G, IT)                                                                  \
+    (paged ? kd_lse_kernel<G, IT, true><<<lse_grid, dim3(64 * kLseWaves), 0, stream>>>(a) \
+           : kd_lse_kernel<G, IT, false><<<lse_grid, dim3(64 * kLseWaves), 0, stream>>>(a))
+#define KD_LSE(G) (per_wave == 1 ? KD_LSE_IT(G, 1) : KD_LSE_IT(G, 2))
+        switch (g.group) {
             case 1: KD_LSE(1); break;
             case 2: KD_LSE(2); break;
             case 4: KD_LSE(4); break;
             case 5: KD_LSE(5); break;
+            case 8: KD_LSE(8); break;
             default: return hipErrorInvalidValue;
         }
 #undef KD_LSE
+#undef KD_LSE_IT
     }
     if (between && hipEventRecord(between, stream) != hipSuccess) return hipErrorUnknown;
     // the target pass: 16-row blocks x (4 waves x kTgtWaveTiles x 64)-key blocks

@@ -137,11 +137,23 @@ def _target_case(w, what, lse_from=None):
 
 @pytest.mark.parametrize("qh,kvh", [(8, 8), (16, 8), (64, 8)])
 def test_target_gqa_groups(qh, kvh):
-    """Groups of 1, 2 and 8 query heads per KV head (the statistics pass takes
-    1, 2 and 2 x 4 heads per workgroup), causal rows across a tile boundary."""
+    """Groups of 1, 2 and 8 query heads per KV head (in the statistics pass 4, 2
+    and half a 32-row block per workgroup), causal rows across a tile boundary."""
     w = inputs.small_workload(batch=1, lens=(333,), n_q=70, causal=True, q_pos0=(263,),
                               q_heads=qh, kv_heads=kvh, n_layers=1, wid=89)
     _target_case(w, f"Hq={qh} Hkv={kvh}")
+
+
+@pytest.mark.parametrize("qh,kvh,nq,layers,ps", [
+    (32, 8, 200, 32, 0),    # 28 items: the last workgroup half empty
+    (20, 4, 300, 40, 64),   # 50 items: a wave's two in different 32-row blocks, a page table
+])
+def test_target_two_items_per_wave(qh, kvh, nq, layers, ps):
+    """At least 1024 workgroups of the statistics pass: two (32 rows, head)
+    items per wave, a last row block with a remainder, causal rows."""
+    w = inputs.small_workload(batch=1, lens=(333,), n_q=nq, causal=True, q_pos0=(333 - nq,),
+                              n_layers=layers, q_heads=qh, kv_heads=kvh, page_size=ps, wid=96)
+    _target_case(w, f"two items per wave, group {qh // kvh}")
 
 
 @pytest.mark.parametrize("lse_from", ["oracle", "dense"])
