@@ -312,6 +312,9 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
         logits(0, s);
         drop(j_begin, MASK ? words(j_begin) : make_uint2(0u, 0u), s);
         rebase(largest(s));
+        // A buffer is stored into only after a barrier that follows its last read: in
+        // the loop the one that ends the step before, for the first step this one.
+        __syncthreads();
         for (int u = 0; u + 1 < tiles; ++u) {
             const int j0 = j_begin + u * kTaKeys, buf = u & 1;
             fetch(a.k, j0 + 2 * kTaKeys, kr);

@@ -1,0 +1,98 @@
+"""The key-tile attention kernel run on the CPU, wave by wave: its results must not
+depend on which wave of a workgroup runs first.  Tolerances as on the GPU."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2606_06467_amd import inputs
+from tests import emu_util
+from tests import gpu_util as U
+
+_WRAPPERS = """
+extern "C" void emu_tile(int batch, int n_q, int max_len, int page_shift, int max_pages, int causal,
+                         int q_heads, int kv_heads, float scale, const void *q, const void *k,
+                         const void *v, const int32_t *pt, const int32_t *sl, const int32_t *qp,
+                         const uint32_t *mask, int splits, int span, void *out, float *lse,
+                         float *po, float *pml, int order) {
+    clsa::Geometry g{batch, n_q, batch * n_q, max_len, page_shift, max_pages, 1, causal,
+                     q_heads, kv_heads, q_heads / kv_heads, scale};
+    emu::wave_order = order;
+    emu::wave_ops = 0;
+    clsa::launch_tile_attn(g, q, k, v, pt, sl, qp, mask, splits, span, out, lse, po, pml, nullptr);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    return emu_util.build(str(tmp_path_factory.mktemp("emu")), "tile_attn.hip", _WRAPPERS)
+
+
+def _p(a):
+    return None if a is None else a.ctypes.data_as(ctypes.c_void_p)
+
+
+def _run(emu, w, x, order, mask=None, scale=None):
+    """(out bits, lse) of one layer, one key range."""
+    q = np.ascontiguousarray(x["q_layers"][0])
+    out = np.zeros(q.shape, np.uint16)
+    lse = np.zeros(q.shape[:-1], np.float32)
+    emu.emu_tile(w.batch, w.n_q, w.max_len, w.page_size.bit_length() - 1, w.max_pages,
+                 int(w.causal), w.q_heads, w.kv_heads,
+                 ctypes.c_float(w.softmax_scale if scale is None else scale), _p(q),
+                 _p(x["k_cache"]), _p(x["v_cache"]), _p(x["page_table"]), _p(x["seq_lens"]),
+                 _p(x["q_pos"]), _p(mask), 1, -(-w.max_len // 64) * 64, _p(out), _p(lse), None,
+                 None, order)
+    return out, lse
+
+
+def _sets(w, x):
+    sh = orc.shape_of(w, top_k=w.max_len)
+    n = orc.valid_lens(sh, x["seq_lens"], x["q_pos"]).astype(np.int32)
+    j = np.arange(w.max_len, dtype=np.int32)
+    return sh, np.where(j < n[..., None], j, -1), n
+
+
+def _compare(w, x, out, lse, sets, what, rows=None):
+    sh, idx, n = sets
+    ref_o, ref_l = orc.sparse_attn(sh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, n,
+                                   x["page_table"])
+    U.compare_attn(out, lse.astype(np.float64), ref_o, ref_l, mask_rows=rows, what=what)
+
+
+def _mask(idx, n, max_len):
+    """The selection words of the kernel: two per 64 keys and row."""
+    bits = np.zeros(idx.shape[:2] + (-(-max_len // 64) * 64,), np.uint8)
+    for r in np.ndindex(n.shape):
+        bits[r][idx[r][:n[r]]] = 1
+    return np.ascontiguousarray(np.packbits(bits, axis=-1, bitorder="little").view(np.uint32))
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("page", [0, 16])
+def test_wave_order_dense(emu, order, page):
+    """Three key tiles, two (row block, head) pairs per KV head: a wave far ahead of
+    the others stores tile after tile while they still read."""
+    w = inputs.small_workload(batch=1, lens=(170,), n_q=40, causal=True, q_pos0=(130,), q_heads=4,
+                              kv_heads=1, page_size=page, n_layers=1, wid=87)
+    x = inputs.make_inputs(w)
+    out, lse = _run(emu, w, x, order)
+    _compare(w, x, out, lse, _sets(w, x), f"waves in order {order}, page {page}")
+
+
+@pytest.mark.parametrize("order", [0, 1])
+def test_wave_order_masked(emu, order):
+    w = inputs.small_workload(batch=1, lens=(150,), n_q=36, causal=True, q_pos0=(114,), q_heads=4,
+                              kv_heads=1, n_layers=1, wid=88)
+    x = inputs.make_inputs(w)
+    sh, idx, n = _sets(w, x)
+    g = np.random.default_rng(88)
+    for r in np.ndindex(n.shape):
+        pick = np.sort(g.choice(n[r], n[r] // 3, replace=False)).astype(np.int32)
+        n[r] = pick.size
+        idx[r] = -1
+        idx[r][:pick.size] = pick
+    out, lse = _run(emu, w, x, order, mask=_mask(idx, n, w.max_len))
+    _compare(w, x, out, lse, (sh, idx, n), f"masked, waves in order {order}")
