@@ -225,6 +225,13 @@ hipError_t launch_kd_target(const Geometry &g, int n_layers, const void *q_layer
 // the loss (before dk).
 bool kd_loss_supported(const Geometry &g);
 size_t kd_loss_ws_floats(const Geometry &g);
+// Ranges (of keys: dq, statistics; of rows: dk), and where the parts of the workspace
+// lie (offsets in floats, and their end, which is within kd_loss_ws_floats).
+struct KdLossPlan {
+    int splits_q, span_q, splits_k, span_k, splits_s, span_s;
+    size_t row_kl, lse2, stats, tile_info, flags, floats;
+};
+KdLossPlan kd_loss_plan(const Geometry &g);
 hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_idx,
                           const void *k_idx, const int32_t *page_table, const int32_t *seq_lens,
                           const int32_t *q_pos, float *loss, float *dq, float *dk, float *ws,

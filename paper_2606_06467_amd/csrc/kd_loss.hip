@@ -71,7 +71,6 @@ struct KdLossArgs {
     int batch, n_q, rows, max_len, page_shift, max_pages, causal;
     int row_tiles;                        // 64-row blocks per sequence
     int blocks, splits, span;             // of the current launch: see the kernels
-    int splits_q, span_q;                 // dq: key ranges, keys per range
 };
 
 __device__ __forceinline__ int row_limit(const KdLossArgs &a, int b, int t) {
@@ -657,12 +656,6 @@ bool kd_loss_supported(const Geometry &g) {
            grid_fits((long long)g.batch * div_up(g.max_len, 64) * 4);
 }
 
-size_t kd_loss_ws_floats(const Geometry &g) {
-    // partials, row terms and statistics: rows * max_len floats hold every split
-    // that kd_splits allows
-    return (size_t)g.rows * g.max_len + g.rows + 2 + (size_t)g.batch * div_up(g.n_q, 32);
-}
-
 // Ranges of the streamed side for `blocks` workgroups of a pass: about
 // kGrWorkgroups in all (causal rows make unequal ranges: 32768 rows 3.8 ms with
 // 2048 workgroups against 4.1 with 1024), each range a multiple of 64 and at least
@@ -677,6 +670,51 @@ static void plan_ranges(long blocks, int length, long most, int &splits, int &sp
     if (want < 1) want = 1;
     span = div_up(tiles, (int)want) * kGrTile;
     splits = div_up(length, span);
+}
+
+size_t kd_loss_ws_floats(const Geometry &g) {
+    return (size_t)g.rows * g.max_len + g.rows + 2 + (size_t)g.batch * div_up(g.n_q, 32);
+}
+
+// Ranges of the passes and the workspace (floats):
+//   [partials of the statistics, then of dq][row terms: splits_q * rows]
+//   [lse2: rows][stats: 2][tile_info][flags].
+// The partials of dk come when the row terms are summed up, and take their place
+// too.  With one range everywhere there are no partials and no flags, which the
+// smallest workspace holds; each further range costs 256 floats and a row term per
+// row (dq) or 256 floats and its flags per token (dk), taken from half of the rest
+// each.  More than kGrMaxList row tiles need several ranges whatever is left: at
+// 16384 rows a range their partials, 256 floats per token, are less than the row
+// terms (16384 per token) even at one key per row, and their flags less than the
+// half of kd_loss_ws_floats' last term that tile_info does not use.
+KdLossPlan kd_loss_plan(const Geometry &g) {
+    KdLossPlan p;
+    const int q_blocks = div_up(g.n_q, kGrBlock), k_blocks = div_up(g.max_len, kGrBlock);
+    const size_t rows = g.rows, tokens = (size_t)g.batch * g.max_len;
+    const size_t room = rows * g.max_len;  // beside one row term per row, stats and tile_info
+    const size_t left = room > rows ? room - rows : 0;
+    const long most_q = (long)(left / (2 * rows * (kIdxDim + 1)));
+    const long most_k = (long)(left / (2 * tokens * (kIdxDim + 1)));
+    plan_ranges((long)g.batch * q_blocks, g.max_len, most_q, p.splits_q, p.span_q);
+    plan_ranges((long)g.batch * k_blocks, g.n_q, most_k, p.splits_k, p.span_k);
+    const int row_list = kGrMaxList * kGrTile;  // rows of one range: the kernel's tile list
+    if (p.span_k > row_list) {
+        p.span_k = row_list;
+        p.splits_k = div_up(g.n_q, row_list);
+    }
+    const int s_blocks = div_up(g.n_q, 32 * kStWaves);
+    plan_ranges((long)g.batch * s_blocks, g.max_len, most_q, p.splits_s, p.span_s);
+    size_t part = 0;
+    if (p.splits_q > 1) part = p.splits_q * rows * kIdxDim;
+    if (p.splits_s > 1 && p.splits_s * rows * 2 > part) part = p.splits_s * rows * 2;
+    p.row_kl = part;
+    p.lse2 = part + p.splits_q * rows;
+    if (p.splits_k > 1 && p.splits_k * tokens * kIdxDim > p.lse2) p.lse2 = p.splits_k * tokens * kIdxDim;
+    p.stats = p.lse2 + rows;
+    p.tile_info = p.stats + 2;
+    p.flags = p.tile_info + (size_t)g.batch * div_up(g.n_q, kGrTile);
+    p.floats = p.flags + (p.splits_k > 1 ? (size_t)p.splits_k * g.batch * k_blocks : 0);
+    return p;
 }
 
 hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_idx,
@@ -702,36 +740,17 @@ hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_id
     a.max_pages = g.max_pages;
     a.causal = g.causal;
     a.row_tiles = div_up(g.n_q, kGrTile);
-    // Workspace: [partials][row terms: splits_q * rows][lse2: rows][stats: 2]
-    // [tile_info][flags].  With one range everywhere there are no partials and
-    // no flags, which the smallest workspace holds; each further range costs 256
-    // floats and a row term per row (dq) or 256 floats per token (dk).
+    const KdLossPlan p = kd_loss_plan(g);
+    if (p.floats > kd_loss_ws_floats(g)) return hipErrorInvalidValue;
     const int q_blocks = div_up(g.n_q, kGrBlock), k_blocks = div_up(g.max_len, kGrBlock);
-    const size_t rows = g.rows, tokens = (size_t)g.batch * g.max_len;
-    const size_t room = rows * g.max_len;  // beside one row term per row, stats and tile_info
-    const size_t left = room > rows ? room - rows : 0;
-    const long most_q = (long)(left / (2 * rows * (kIdxDim + 1)));
-    const long most_k = (long)(left / (2 * tokens * (kIdxDim + 1)));
-    int splits_k, span_k, splits_s, span_s;
-    plan_ranges((long)g.batch * q_blocks, g.max_len, most_q, a.splits_q, a.span_q);
-    plan_ranges((long)g.batch * k_blocks, g.n_q, most_k, splits_k, span_k);
-    const int row_list = kGrMaxList * kGrTile;  // rows of one range: the kernel's tile list
-    if (span_k > row_list) {
-        span_k = row_list;
-        splits_k = div_up(g.n_q, span_k);
-    }
     const int s_blocks = div_up(g.n_q, 32 * kStWaves);
-    plan_ranges((long)g.batch * s_blocks, g.max_len, most_q, splits_s, span_s);
-    size_t part = 0;
-    if (a.splits_q > 1) part = a.splits_q * rows * kIdxDim;
-    if (splits_k > 1 && splits_k * tokens * kIdxDim > part) part = splits_k * tokens * kIdxDim;
-    if (splits_s > 1 && splits_s * rows * 2 > part) part = splits_s * rows * 2;
+    const size_t rows = g.rows, tokens = (size_t)g.batch * g.max_len;
     a.part = ws;
-    a.row_kl = ws + part;
-    a.lse2 = a.row_kl + a.splits_q * rows;
-    a.stats = a.lse2 + rows;
-    a.tile_info = reinterpret_cast<uint32_t *>(a.stats + 2);
-    a.flags = reinterpret_cast<int32_t *>(a.tile_info) + (size_t)g.batch * a.row_tiles;
+    a.row_kl = ws + p.row_kl;
+    a.lse2 = ws + p.lse2;
+    a.stats = ws + p.stats;
+    a.tile_info = reinterpret_cast<uint32_t *>(ws + p.tile_info);
+    a.flags = reinterpret_cast<int32_t *>(ws + p.flags);
     const bool paged = g.page_shift >= 0;
 #define KD_LAUNCH(KERNEL, GRID, THREADS) \
     KERNEL<<<dim3((unsigned)(GRID)), dim3(THREADS), 0, stream>>>(a)
@@ -744,17 +763,17 @@ hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_id
         KD_LAUNCH(kd_count_kernel, 1, 1024);
     }
     a.blocks = s_blocks;
-    a.splits = splits_s;
-    a.span = span_s;
-    const long s_grid = (long)g.batch * s_blocks * splits_s;
+    a.splits = p.splits_s;
+    a.span = p.span_s;
+    const long s_grid = (long)g.batch * s_blocks * p.splits_s;
     if (paged) KD_LAUNCH(kd_stats_kernel<true>, s_grid, 64 * kStWaves);
     else KD_LAUNCH(kd_stats_kernel<false>, s_grid, 64 * kStWaves);
     if (a.splits > 1) KD_LAUNCH(kd_stats_merge_kernel, div_up(g.rows, 256), 256);
     if (after_scores && hipEventRecord(after_scores, stream) != hipSuccess) return hipErrorUnknown;
 
     a.blocks = q_blocks;
-    a.splits = a.splits_q;
-    a.span = a.span_q;
+    a.splits = p.splits_q;
+    a.span = p.span_q;
     const long q_grid = (long)g.batch * q_blocks * a.splits;
     if (paged) KD_LAUNCH((kd_grad_kernel<false, true>), q_grid, 256);
     else KD_LAUNCH((kd_grad_kernel<false, false>), q_grid, 256);
@@ -763,8 +782,8 @@ hipError_t launch_kd_loss(const Geometry &g, const float *abar, const void *q_id
     if (after_loss && hipEventRecord(after_loss, stream) != hipSuccess) return hipErrorUnknown;
 
     a.blocks = k_blocks;
-    a.splits = splits_k;
-    a.span = span_k;
+    a.splits = p.splits_k;
+    a.span = p.span_k;
     const long k_grid = (long)g.batch * k_blocks * a.splits;
     if (paged) KD_LAUNCH((kd_grad_kernel<true, true>), k_grid, 256);
     else KD_LAUNCH((kd_grad_kernel<true, false>), k_grid, 256);

@@ -490,3 +490,12 @@ def test_loss_values_not_finite_stay_with_their_pairs(side):
         np.testing.assert_allclose(q1[keep], q0[keep], rtol=0, atol=1e-6 * np.abs(q0).max())
         np.testing.assert_allclose(k1[301:], k0[301:], rtol=0, atol=1e-6 * np.abs(k0).max())
         assert not np.isfinite(k1[:301]).any()
+
+
+@pytest.mark.parametrize("n", [1, 3])
+def test_loss_rows_past_one_tile_list(n):
+    """More than 16384 rows of one sequence over a key or three: two ranges of rows in
+    the smallest workspace."""
+    w = inputs.small_workload(batch=1, lens=(n,), n_q=16385, n_layers=1, q_heads=8, kv_heads=8,
+                              wid=104)
+    _loss_case(w, f"16385 rows of {n} keys", abar64=_peaked(w))
