@@ -37,6 +37,8 @@
 #include "clsa_internal.h"
 #include "device_common.h"
 
+#include <math.h>
+
 namespace clsa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -62,7 +64,7 @@ struct TileAttnArgs {
     int group, row_blocks; // query heads per KV head, blocks of NW (32 rows, head) pairs per sequence
     int splits, span;      // key ranges per row, keys per range (a multiple of kTaKeys)
     int mask_pitch;        // words per row (two per tile)
-    float scale_log2;
+    float scale_log2, q_sign;  // scale_log2 > 0: see launch_tile_attn
 };
 
 // Maximum / sum over the two lanes of a query (l and l ^ 32).
@@ -111,7 +113,7 @@ __device__ __forceinline__ void tile_attn_rows(const TileAttnArgs &a, int b, int
             const uint32_t kw = *reinterpret_cast<const uint32_t *>(a.k + off);
             const uint32_t vw = *reinterpret_cast<const uint32_t *>(a.v + off);
             const float z = wave_sum(fmaf(bf16_lo(kw), bf16_lo(qw), bf16_hi(kw) * bf16_hi(qw))) *
-                            a.scale_log2;
+                            (a.scale_log2 * a.q_sign);
             const float nm = fmaxf(m, z), base = nm == -INFINITY ? 0.0f : nm;
             const float f = __builtin_amdgcn_exp2f(m - base), w = __builtin_amdgcn_exp2f(z - base);
             l = fmaf(l, f, w);
@@ -165,6 +167,11 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
 #pragma unroll
         for (int s = 0; s < 8; ++s)
             qb[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p + 16 * s));
+        if (a.q_sign != 1.0f)  // uniform
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) qb[s][e] = (__bf16)((float)qb[s][e] * a.q_sign);
     }
     __syncthreads();
     int wg_max = s_lim[0];
@@ -476,7 +483,12 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
     a.splits = splits;
     a.span = span;
     a.mask_pitch = mask_words(g);
-    a.scale_log2 = g.softmax_scale * 1.4426950408889634f;
+    // The kernel drops keys (-inf) and takes maxima before it scales, so its scale is
+    // positive: the sign of the caller's goes into the queries (exact), and a scale of
+    // zero makes them zero.
+    const float scale = g.softmax_scale;
+    a.q_sign = scale > 0.0f ? 1.0f : scale < 0.0f ? -1.0f : 0.0f;
+    a.scale_log2 = scale == 0.0f ? 1.0f : fabsf(scale) * 1.4426950408889634f;
     const size_t blocks = (size_t)g.batch * a.row_blocks * g.kv_heads * splits;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;

@@ -116,3 +116,36 @@ def test_step_selection_excludes_values_not_finite(ps):
     ro, rl = orc.sparse_attn(orc.shape_of(w), x["q_layers"][0], x["k_cache"], x["v_cache"], idx,
                              ns, x["page_table"])
     U.compare_attn(out[0], lse[0], ro, rl, mask_rows=~has[None])
+
+
+@pytest.mark.parametrize("scale", [0.0, -0.09])
+def test_scale_not_positive(scale):
+    """Dense rows in tiles and in the per-row kernel, and a step with selection masks."""
+    import torch
+    from paper_2606_06467_amd import binding as B
+    for nq, n, top_k in ((70, 1900, 64), (5, 1900, 64), (1000, 1000, 600)):
+        w = inputs.small_workload(batch=1, lens=(n,), n_q=nq, causal=True, q_pos0=(n - nq,),
+                                  top_k=top_k, n_layers=1, wid=89)
+        x = inputs.make_inputs(w)
+        sh = U.shape_of(w)
+        sh.softmax_scale = scale
+        d = U.to_dev(x)
+        q = d["q_layers"]
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+        lse = torch.full(q.shape[:-1], float("nan"), device="cuda")
+        if nq < 1000:
+            B.clsa_dense_attn(sh, q[0], d["k_cache"], d["v_cache"], None, d["seq_lens"],
+                              d["q_pos"], out[0], lse[0], B.workspace(sh, B.CLSA_OP_DENSE))
+            osh, idx, ns = _full_sets(w, x["seq_lens"], x["q_pos"])
+        else:
+            idx = torch.empty((1, nq, top_k), dtype=torch.int32, device="cuda")
+            ns = torch.empty((1, nq), dtype=torch.int32, device="cuda")
+            B.clsa_decode_step(sh, d["q_idx"], d["k_idx"], d["k_cache"], d["v_cache"], None,
+                               d["seq_lens"], d["q_pos"], q, out, lse, idx, ns,
+                               B.workspace(sh, B.CLSA_OP_DECODE, 1))
+            osh, idx, ns = orc.shape_of(w), idx.cpu().numpy(), ns.cpu().numpy()
+        torch.cuda.synchronize()
+        osh.softmax_scale = scale
+        ref_o, ref_l = orc.sparse_attn(osh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, ns)
+        U.compare_attn(B.bits_from_bf16(out[0]), lse[0].cpu().numpy().astype(np.float64), ref_o,
+                       ref_l, what=f"scale {scale}, {nq} rows")

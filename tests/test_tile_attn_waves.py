@@ -22,6 +22,7 @@ extern "C" void emu_tile(int batch, int n_q, int max_len, int page_shift, int ma
     emu::wave_ops = 0;
     clsa::launch_tile_attn(g, q, k, v, pt, sl, qp, mask, splits, span, out, lse, po, pml, nullptr);
 }
+extern "C" long emu_wave_ops() { return emu::wave_ops; }
 """
 
 
@@ -55,8 +56,10 @@ def _sets(w, x):
     return sh, np.where(j < n[..., None], j, -1), n
 
 
-def _compare(w, x, out, lse, sets, what, rows=None):
+def _compare(w, x, out, lse, sets, what, rows=None, scale=None):
     sh, idx, n = sets
+    if scale is not None:
+        sh.softmax_scale = scale
     ref_o, ref_l = orc.sparse_attn(sh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, n,
                                    x["page_table"])
     U.compare_attn(out, lse.astype(np.float64), ref_o, ref_l, mask_rows=rows, what=what)
@@ -68,6 +71,15 @@ def _mask(idx, n, max_len):
     for r in np.ndindex(n.shape):
         bits[r][idx[r][:n[r]]] = 1
     return np.ascontiguousarray(np.packbits(bits, axis=-1, bitorder="little").view(np.uint32))
+
+
+def _thirds(idx, n):
+    """A third of every row's keys."""
+    g = np.random.default_rng(88)
+    idx, n = np.full_like(idx, -1), n // 3
+    for r in np.ndindex(n.shape):
+        idx[r][:n[r]] = np.sort(g.choice(3 * n[r], n[r], replace=False))
+    return idx, n
 
 
 @pytest.mark.parametrize("order", [0, 1])
@@ -88,11 +100,26 @@ def test_wave_order_masked(emu, order):
                               kv_heads=1, n_layers=1, wid=88)
     x = inputs.make_inputs(w)
     sh, idx, n = _sets(w, x)
-    g = np.random.default_rng(88)
-    for r in np.ndindex(n.shape):
-        pick = np.sort(g.choice(n[r], n[r] // 3, replace=False)).astype(np.int32)
-        n[r] = pick.size
-        idx[r] = -1
-        idx[r][:pick.size] = pick
+    idx, n = _thirds(idx, n)
     out, lse = _run(emu, w, x, order, mask=_mask(idx, n, w.max_len))
     _compare(w, x, out, lse, (sh, idx, n), f"masked, waves in order {order}")
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("scale", [0.0, -0.09])
+def test_scale_not_positive(emu, scale, masked):
+    """A scale of zero weighs every key alike, a negative one turns the order round; both
+    take the same work as a positive one."""
+    w = inputs.small_workload(batch=1, lens=(150,), n_q=36, causal=True, q_pos0=(114,), q_heads=4,
+                              kv_heads=1, n_layers=1, wid=88)
+    x = inputs.make_inputs(w)
+    sh, idx, n = _sets(w, x)
+    mask = None
+    if masked:
+        idx, n = _thirds(idx, n)
+        mask = _mask(idx, n, w.max_len)
+    _run(emu, w, x, 0, mask=mask)
+    usual = emu.emu_wave_ops()
+    out, lse = _run(emu, w, x, 0, mask=mask, scale=scale)
+    _compare(w, x, out, lse, (sh, idx, n), f"scale {scale}", scale=scale)
+    assert emu.emu_wave_ops() <= 1.1 * usual
