@@ -21,8 +21,16 @@
 //     slot (hi, j) of a 16-key step stands for key 4 hi + (j & 3) + 8 (j >> 2)),
 //     so they never leave their registers; A = V^T by ds_read_b64_tr_b16, the
 //     transposing LDS read, from the row-major value tile.
-// The running maximum moves lazily: only when a logit exceeds it by 2^kTaLazy
-// (a wave-uniform branch), so that the steady state rescales nothing.
+// The weights enter the second product as bf16, so each tile has its own base: the
+// largest logit of the row in that tile (not more than kTaLag below the row's
+// largest so far), whose weight is then 1 exactly, and the accumulators move from
+// base to base.  The row's first tile adds what rounding takes from its weights as a
+// second product, since short rows have few keys and large weights.  Error of the
+// outputs against 64 bits (their own rounding alone makes 0.00166), 8192 causal rows /
+// 1000 rows of 6000 keys, 2048 selected: 0.00185 / 0.00199; with one base per row that
+// lags by up to 2^8 0.0021 / 0.0023; every row gathering its own keys, whose list is
+// cut into eight ranges with a base each, 0.00205 / 0.00213.  The sum of the weights
+// keeps the row's largest logit as its base, so that it is not rounded at every tile.
 // What bounds it: a wave alternates matrix products and the exponentials that
 // depend on them, at two waves per SIMD (the accumulators, queries and two
 // tiles' logits fill 256 registers).  The loop is therefore pipelined by one
@@ -32,8 +40,9 @@
 // FLOP): every row gathering its own keys 2.7-2.8 ms (127 TFLOP/s); these tiles
 // with the steps of a tile one after another, one wave per head, 0.56; pipelined
 // with four waves per workgroup 0.46, with eight 0.41, and the key registers
-// stored between the two halves (no spill) 0.397 ms: 860 TFLOP/s, 71% of what
-// the library GEMM reaches on 8192^3 (1216).
+// stored between the two halves (no spill) 0.394; a base per tile 0.410, and with
+// the loop unrolled by two, so that a tile's logits are not copied, 0.391 ms:
+// 870 TFLOP/s, 72% of what the library GEMM reaches on 8192^3 (1216).
 #include "clsa_internal.h"
 #include "device_common.h"
 
@@ -50,7 +59,7 @@ constexpr int kTaDim = 128;
 constexpr int kTaKeys = 64;              // keys per tile
 constexpr int kTaKPitch = kTaDim + 8;    // bf16 per staged key row (272 bytes)
 constexpr int kTaVPitch = kTaDim + 16;   // bf16 per staged value row (288 bytes)
-constexpr float kTaLazy = 8.0f;          // log2 units the maximum may lag behind
+constexpr float kTaLag = 8.0f;           // log2 units a tile's base may lie below the row's maximum
 constexpr float kTaLn2 = 0.6931471805599453f;
 
 struct TileAttnArgs {
@@ -67,10 +76,16 @@ struct TileAttnArgs {
     float scale_log2, q_sign;  // scale_log2 > 0: see launch_tile_attn
 };
 
+// IEEE maximum (gfx950 v_maximum3_f32; no operand canonicalisation).  A logit that is
+// NaN makes its row NaN either way.
+__device__ __forceinline__ float ta_max(float x, float y) {
+    return __builtin_elementwise_maximum(x, y);
+}
+
 // Maximum / sum over the two lanes of a query (l and l ^ 32).
 __device__ __forceinline__ float pair_max(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    return ta_max(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float pair_sum(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -186,7 +201,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
     for (int d = 0; d < 4; ++d)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
-    float m = -INFINITY, l = 0.0f;
+    float m = -INFINITY, top = -INFINITY, l = 0.0f;  // base of o, maximum so far (base of l)
 
     // staging: thread -> 16-byte piece (tid & 15) of key rows (tid >> 4) + i * NT / 16;
     // keys past len are clamped (and masked)
@@ -261,22 +276,22 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
         }
     };
     auto largest = [&](const f32x16 (&s)[2]) {
-        float mx = fmaxf(s[0][0], s[1][0]);
+        float mx = ta_max(s[0][0], s[1][0]);
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(s[0][r], s[1][r]));
+        for (int r = 1; r < 16; ++r) mx = ta_max(ta_max(mx, s[0][r]), s[1][r]);
         return pair_max(mx * a.scale_log2);
     };
-    auto rebase = [&](float mx) {
-        if (__builtin_amdgcn_ballot_w64(mx > m + kTaLazy)) {
-            const float nm = fmaxf(m, mx);
-            const float f = nm == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - nm);
-            m = nm;
-            l *= f;
+    auto rebase = [&](float mx) {  // mx: the next tile's largest logit
+        const float old = top;
+        top = ta_max(top, mx);
+        const float nm = ta_max(mx, top - kTaLag);
+        const float f = nm == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - nm);
+        l *= top == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(old - top);
+        m = nm;
 #pragma unroll
-            for (int d = 0; d < 4; ++d)
+        for (int d = 0; d < 4; ++d)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[d][r] *= f;
-        }
+            for (int r = 0; r < 16; ++r) o[d][r] *= f;
     };
     auto weights = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4]) {
         const float base = m == -INFINITY ? 0.0f : m;
@@ -289,7 +304,17 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
                 sum[kt] += p;
                 pb[2 * kt + (r >> 3)][r & 7] = (__bf16)p;
             }
-        l += sum[0] + sum[1];
+        l = fmaf(sum[0] + sum[1], m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - top), l);
+    };
+    auto residues = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4]) {  // what weights() rounds off
+        const float base = m == -INFINITY ? 0.0f : m;
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[kt][r], a.scale_log2, -base));
+                pb[2 * kt + (r >> 3)][r & 7] = (__bf16)(p - (float)(__bf16)p);
+            }
     };
     auto weighted = [&](int buf, const bf16x8 (&pb)[4]) {
 #pragma unroll
@@ -319,15 +344,20 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
         logits(0, s);
         drop(j_begin, MASK ? words(j_begin) : make_uint2(0u, 0u), s);
         rebase(largest(s));
+        {  // the first tile's weights keep 16 bits
+            bf16x8 pb[4];
+            residues(s, pb);
+            weighted(0, pb);
+        }
         // A buffer is stored into only after a barrier that follows its last read: in
         // the loop the one that ends the step before, for the first step this one.
         __syncthreads();
-        for (int u = 0; u + 1 < tiles; ++u) {
+        f32x16 sn[2];
+        auto step = [&](int u, const f32x16 (&s)[2], f32x16 (&sn)[2]) {
             const int j0 = j_begin + u * kTaKeys, buf = u & 1;
             fetch(a.k, j0 + 2 * kTaKeys, kr);
             fetch(a.v, j0 + kTaKeys, vr);
             const uint2 w = MASK ? words(j0 + kTaKeys) : make_uint2(0u, 0u);
-            f32x16 sn[2];
             bf16x8 pb[4];
             __builtin_amdgcn_sched_barrier(0);
             logits(buf ^ 1, sn);
@@ -341,15 +371,32 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
             stage_v(buf ^ 1, vr);
             rebase(mx);
             __syncthreads();
-            s[0] = sn[0];
-            s[1] = sn[1];
+        };
+        auto last = [&](const f32x16 (&s)[2]) {
+            bf16x8 pb[4];
+            weights(s, pb);
+            weighted((tiles - 1) & 1, pb);
+        };
+        int u = 0;
+        for (; u + 2 < tiles; u += 2) {
+            step(u, s, sn);
+            step(u + 1, sn, s);
         }
-        bf16x8 pb[4];
-        weights(s, pb);
-        weighted((tiles - 1) & 1, pb);
+        if (u + 1 < tiles) {
+            step(u, s, sn);
+            last(sn);
+        } else {
+            last(s);
+        }
     }
     if (t0 >= a.n_q) return;
     l = pair_sum(l);
+    const float to_top = m == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - top);
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[d][r] *= to_top;
+    m = top;
     // a value that is not finite in any result of the wave: see tile_attn_rows
     float odd = 0.0f;
 #pragma unroll
