@@ -97,57 +97,13 @@ __device__ __forceinline__ int wave_max_i(int x) {
     for (int d = 1; d < 64; d <<= 1) x = max(x, __shfl_xor(x, d));
     return x;
 }
+// Not an infinity and not a NaN.
+__device__ __forceinline__ bool finite(float x) { return x - x == 0.0f; }
+
 __device__ __forceinline__ int wave_min_i(int x) {
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) x = min(x, __shfl_xor(x, d));
     return x;
-}
-
-// The wave's queries one by one, one key at a time (2 dimensions per lane),
-// every value exactly as selected: taken only when a tile product met an
-// infinity or a NaN, which a weight of zero does not remove from a product, so
-// that a key outside a row's set never reaches its result.
-template <bool PAGED, bool MASK>
-__device__ __forceinline__ void tile_attn_rows(const TileAttnArgs &a, int b, int t0, int g, int h,
-                                            int split) {
-    const int lane = threadIdx.x & 63;
-    for (int i = 0; i < 32 && t0 + i < a.n_q; ++i) {
-        const int row = b * a.n_q + t0 + i;
-        const int n = valid_keys(a.seq_lens, a.q_pos, a.causal, b, row, a.max_len);
-        const int j_end = min(n, (split + 1) * a.span);
-        const uint32_t qw = *reinterpret_cast<const uint32_t *>(
-            a.q + ((size_t)row * a.q_heads + h) * kTaDim + 2 * lane);
-        float m = -INFINITY, l = 0.0f, ox = 0.0f, oy = 0.0f;
-        for (int j = split * a.span; j < j_end; ++j) {
-            if (MASK) {
-                if (!((a.mask[(size_t)row * a.mask_pitch + (j >> 5)] >> (j & 31)) & 1u))
-                    continue;  // uniform
-            }
-            const size_t off = token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b, j,
-                                            a.kv_heads * kTaDim) + (size_t)g * kTaDim + 2 * lane;
-            const uint32_t kw = *reinterpret_cast<const uint32_t *>(a.k + off);
-            const uint32_t vw = *reinterpret_cast<const uint32_t *>(a.v + off);
-            const float z = wave_sum(fmaf(bf16_lo(kw), bf16_lo(qw), bf16_hi(kw) * bf16_hi(qw))) *
-                            (a.scale_log2 * a.q_sign);
-            const float nm = fmaxf(m, z), base = nm == -INFINITY ? 0.0f : nm;
-            const float f = __builtin_amdgcn_exp2f(m - base), w = __builtin_amdgcn_exp2f(z - base);
-            l = fmaf(l, f, w);
-            ox = fmaf(w, bf16_lo(vw), ox * f);
-            oy = fmaf(w, bf16_hi(vw), oy * f);
-            m = nm;
-        }
-        const size_t rh = (size_t)row * a.q_heads + h;
-        if (a.splits > 1 && n > 0) {
-            const size_t slot = rh * a.splits + split;
-            *reinterpret_cast<float2 *>(a.part_o + slot * kTaDim + 2 * lane) = make_float2(ox, oy);
-            if (lane == 0) *reinterpret_cast<float2 *>(a.part_ml + slot * 2) = make_float2(m, l);
-        } else if (split == 0) {
-            const float inv = n == 0 ? 0.0f : 1.0f / l;
-            const bf16x2 o = {(__bf16)(ox * inv), (__bf16)(oy * inv)};
-            *reinterpret_cast<uint32_t *>(a.out + rh * kTaDim + 2 * lane) = __builtin_bit_cast(uint32_t, o);
-            if (a.lse && lane == 0) a.lse[rh] = (m + log2f(l)) * kTaLn2;
-        }
-    }
 }
 
 template <int NW, bool PAGED, bool MASK>
@@ -206,19 +162,21 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
     // staging: thread -> 16-byte piece (tid & 15) of key rows (tid >> 4) + i * NT / 16;
     // keys past len are clamped (and masked)
     const int srow = tid >> 4, spc = (tid & 15) * 8;
+    auto vector_at = [&](const uint16_t *base, int j) {  // key or value j (at most the last)
+        j = min(j, len - 1);
+        size_t tok;
+        if (PAGED) {
+            const int page = a.page_table[(size_t)b * a.max_pages + (j >> a.page_shift)];
+            tok = ((size_t)page << a.page_shift) + (j & ((1 << a.page_shift) - 1));
+        } else {
+            tok = (size_t)b * a.max_len + j;
+        }
+        return base + (tok * a.kv_heads + g) * kTaDim;
+    };
     auto fetch = [&](const uint16_t *base, int j0, u32x4 (&v)[PER]) {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int j = min(j0 + srow + i * (NT / 16), len - 1);
-            size_t tok;
-            if (PAGED) {
-                const int page = a.page_table[(size_t)b * a.max_pages + (j >> a.page_shift)];
-                tok = ((size_t)page << a.page_shift) + (j & ((1 << a.page_shift) - 1));
-            } else {
-                tok = (size_t)b * a.max_len + j;
-            }
-            v[i] = *reinterpret_cast<const u32x4 *>(base + (tok * a.kv_heads + g) * kTaDim + spc);
-        }
+        for (int i = 0; i < PER; ++i)
+            v[i] = *reinterpret_cast<const u32x4 *>(vector_at(base, j0 + srow + i * (NT / 16)) + spc);
     };
     auto stage_k = [&](int buf, const u32x4 (&v)[PER]) {
 #pragma unroll
@@ -281,10 +239,10 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
         for (int r = 1; r < 16; ++r) mx = ta_max(ta_max(mx, s[0][r]), s[1][r]);
         return pair_max(mx * a.scale_log2);
     };
-    auto rebase = [&](float mx) {  // mx: the next tile's largest logit
+    auto rebase = [&](float mx, float lag) {  // mx: the next tile's largest logit
         const float old = top;
         top = ta_max(top, mx);
-        const float nm = ta_max(mx, top - kTaLag);
+        const float nm = ta_max(mx, top - lag);
         const float f = nm == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - nm);
         l *= top == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(old - top);
         m = nm;
@@ -343,7 +301,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
         f32x16 s[2];
         logits(0, s);
         drop(j_begin, MASK ? words(j_begin) : make_uint2(0u, 0u), s);
-        rebase(largest(s));
+        rebase(largest(s), kTaLag);
         {  // the first tile's weights keep 16 bits
             bf16x8 pb[4];
             residues(s, pb);
@@ -369,7 +327,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
             const float mx = largest(sn);
             __builtin_amdgcn_sched_barrier(0);
             stage_v(buf ^ 1, vr);
-            rebase(mx);
+            rebase(mx, kTaLag);
             __syncthreads();
         };
         auto last = [&](const f32x16 (&s)[2]) {
@@ -389,7 +347,114 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
             last(s);
         }
     }
+    __syncthreads();  // every wave is done with the tiles: see below
     if (t0 >= a.n_q) return;
+    // A value that is not finite reaches the products of rows without its key (a
+    // weight of zero does not remove it), and one near the largest float can overflow
+    // the tiles' lagging base.  A wave with such a result of finite logits makes it
+    // again, each value reaching the rows of its key alone: keys straight from memory,
+    // values 32 at a time through the wave's own eighth of the tiles, those that are
+    // not finite staged as zeros and added by hand, the base always the row's
+    // maximum.  8192 causal rows with one infinity 1.9 ms, 64 rows x 131072 keys 1.0
+    // (0.4 and 0.19 without); one key at a time it was hundreds of times the usual.
+    float odd = 0.0f;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) odd = fmaf(o[d][r], 0.0f, odd);
+    const float l_both = pair_sum(l);
+    const bool again = odd != 0.0f && finite(l_both) && (n > j_begin || n == 0) && t < a.n_q;
+    if (__builtin_amdgcn_ballot_w64(again)) {
+        static_assert(NW == 8, "eight slots of 32 rows in the tiles");
+        typedef __attribute__((address_space(3))) u32x4 lds16;
+        typedef __attribute__((address_space(3))) s16x4 lds4;
+        uint16_t *own = wave < 4 ? &s_k[wave >> 1][32 * (wave & 1)][0]
+                                 : &s_v[(wave - 4) >> 1][32 * (wave & 1)][0];
+        const int pitch = wave < 4 ? kTaKPitch : kTaVPitch;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
+        m = top = -INFINITY;
+        l = 0.0f;
+        for (int j0 = j_begin; j0 < min(nmax, j_begin + a.span); j0 += kTaKeys) {
+            f32x16 s[2];
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                const uint16_t *kp = vector_at(a.k, j0 + 32 * kt + col) + 8 * hi;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[kt][r] = 0.0f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks)
+                    s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kp + 16 * ks)), qb[ks],
+                        s[kt], 0, 0, 0);
+            }
+            const uint2 w = MASK ? words(j0) : make_uint2(0u, 0u);
+            drop(j0, w, s);
+            rebase(largest(s), 0.0f);
+            bf16x8 pb[4], pr[4];
+            weights(s, pb);
+            residues(s, pr);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                uint32_t bad = 0u;  // keys of the half tile with a value that is not finite
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int r = 4 * i + (lane >> 4);
+                    u32x4 x = *reinterpret_cast<const u32x4 *>(vector_at(a.v, j0 + 32 * kt + r) + (lane & 15) * 8);
+                    bool some = false;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool lo = finite(bf16_lo(x[e])), up = finite(bf16_hi(x[e]));
+                        some |= !lo || !up;
+                        x[e] &= (lo ? 0x0000ffffu : 0u) | (up ? 0xffff0000u : 0u);
+                    }
+                    *(lds16 *)(own + r * pitch + (lane & 15) * 8) = x;
+                    const uint64_t rows = __builtin_amdgcn_ballot_w64(some);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        bad |= ((uint32_t)(rows >> (16 * q)) & 0xffffu ? 1u : 0u) << (4 * i + q);
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const uint16_t *v = own + (16 * kb + vrow) * pitch + 32 * d + vcol;
+                        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4 *)v);
+                        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4 *)(v + 8 * pitch));
+                        const bf16x8 va = __builtin_bit_cast(
+                            bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+                        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[2 * kt + kb], o[d], 0, 0, 0);
+                        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pr[2 * kt + kb], o[d], 0, 0, 0);
+                    }
+                __builtin_amdgcn_wave_barrier();
+                for (; bad; bad &= bad - 1u) {  // uniform
+                    const int i = __builtin_ctz(bad), j = j0 + 32 * kt + i;
+                    const bool in = j < n && (!MASK || (((kt ? w.y : w.x) >> i) & 1u));
+                    float z = s[kt][0];  // the key's logit: register 4 (i >> 3) + (i & 3) of lanes hi = (i >> 2) & 1
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) z = r == 4 * (i >> 3) + (i & 3) ? s[kt][r] : z;
+                    const uint32_t p = __float_as_uint(__builtin_amdgcn_exp2f(fmaf(z, a.scale_log2, -m)));
+                    const auto both = __builtin_amdgcn_permlane32_swap(p, p, false, false);
+                    const float wt = __uint_as_float(both[0]), wu = __uint_as_float(both[1]);
+                    const uint16_t *vp = vector_at(a.v, j) + 4 * hi;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d)
+#pragma unroll
+                        for (int r = 0; r < 16; r += 4) {
+                            const u32x2 x = *reinterpret_cast<const u32x2 *>(vp + 32 * d + 2 * r);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                const float v = c & 1 ? bf16_hi(x[c >> 1]) : bf16_lo(x[c >> 1]);
+                                if (in && !finite(v)) o[d][r + c] = fmaf((i >> 2) & 1 ? wu : wt, v, o[d][r + c]);
+                            }
+                        }
+                }
+            }
+        }
+    }
     l = pair_sum(l);
     const float to_top = m == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - top);
 #pragma unroll
@@ -397,16 +462,6 @@ __global__ __launch_bounds__(64 * NW, 2) void tile_attn_kernel(TileAttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[d][r] *= to_top;
     m = top;
-    // a value that is not finite in any result of the wave: see tile_attn_rows
-    float odd = 0.0f;
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) odd = fmaf(o[d][r], 0.0f, odd);
-    if (__builtin_amdgcn_ballot_w64(odd != 0.0f || l != l)) {
-        tile_attn_rows<PAGED, MASK>(a, b, t0, g, h, split);
-        return;
-    }
     if (t >= a.n_q) return;
     const size_t rh = (size_t)row * a.q_heads + h;
     if (a.splits > 1 && n > 0) {

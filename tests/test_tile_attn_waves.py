@@ -172,3 +172,51 @@ def test_short_rows_are_as_exact_as_their_outputs(emu):
     d = inputs.f32_from_bf16_bits(out).astype(np.float64) - ref
     rel = float(np.sqrt((d * d).sum() / (ref * ref).sum()))
     assert rel < 0.00175, rel
+
+
+def _float_model(w, x, idx, n):
+    """Attention with every value as it is: out, in float64 (infinities and NaN included)."""
+    q, k, v = (inputs.f32_from_bf16_bits(x[i]).astype(np.float64) for i in ("q_layers", "k_cache", "v_cache"))
+    if w.page_size:
+        k, v = (c[x["page_table"][0]].reshape((-1,) + c.shape[2:])[None] for c in (k, v))
+    out = np.zeros(q[0].shape)
+    with np.errstate(all="ignore"):
+        for t in range(w.n_q):
+            s = idx[0, t, :n[0, t]]
+            z = q[0, 0, t] @ k[0, s, 0].T * w.softmax_scale
+            e = np.exp(z - z.max(-1, keepdims=True))
+            out[0, t] = (e[:, :, None] * v[0, s, 0][None]).sum(1) / e.sum(-1, keepdims=True)
+    return out
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.3e38])
+def test_values_not_finite(emu, bad, masked, page):
+    """One value of three keys (the first of the sequence, one that some rows see, the
+    last) is not finite, or so large that sums of a lagging base overflow: the outputs
+    are those of every value as it is, for at most a few times the work."""
+    w = inputs.small_workload(batch=1, lens=(176,), n_q=70, causal=True, q_pos0=(106,), q_heads=4,
+                              kv_heads=1, page_size=page, n_layers=1, wid=92)
+    x = inputs.make_inputs(w)
+    sh, idx, n = _sets(w, x)
+    mask = None
+    if masked:
+        idx, n = _thirds(idx, n)
+        mask = _mask(idx, n, w.max_len)
+    _run(emu, w, x, 0, mask=mask)
+    usual = emu.emu_wave_ops()
+    x["v_cache"] = x["v_cache"].copy()
+    for j, d in ((0, 3), (130, 77), (175, 127)):
+        at = (x["page_table"][0, j // page], j % page) if page else (0, j)
+        x["v_cache"][at][0, d] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
+    out, lse = _run(emu, w, x, 0, mask=mask)
+    assert emu.emu_wave_ops() <= 4 * usual
+    o, ref = inputs.f32_from_bf16_bits(out).astype(np.float64), _float_model(w, x, idx, n)
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isnan(o), np.isnan(ref))
+    assert np.array_equal(o[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)])
+    assert np.all(np.abs(o[fin] - ref[fin]) <= 0.02 * np.maximum(1, np.abs(ref[fin])))
+    _, ref_l = orc.sparse_attn(sh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, n,
+                               x["page_table"])
+    assert np.abs(lse - ref_l).max() < 1e-4
