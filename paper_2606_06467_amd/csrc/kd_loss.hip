@@ -305,42 +305,8 @@ __device__ __forceinline__ float *grad_dst(const KdLossArgs &a, int b, int x, in
               : a.dq + ((size_t)b * a.n_q + x) * kIdxDim;
 }
 
-// The gradient of the wave's own 32 vectors one by one, in fp32, from the pairs
-// that count alone: taken only when a product met an infinity or a NaN, which a
-// weight of zero does not remove from it, so that a vector reaches the gradients
-// of those that it meets and no others.  Four dimensions per lane.
-template <bool DK>
-__device__ __forceinline__ void kd_grad_exact(const KdLossArgs &a, int b, int x0, int own, int y_begin,
-                                              int y_end, float f, int split) {
-    const int lane = threadIdx.x & 63;
-    const int rows = a.n_q, len = clamp_len(a.seq_lens[b], a.max_len);
-    for (int i = 0; i < 32 && x0 + i < own; ++i) {
-        const int x = x0 + i;
-        const int lim = DK ? min(rows, y_end) : min(min(y_end, row_limit(a, b, x)), len);
-        const size_t xo = DK ? token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b, x, kIdxDim)
-                             : ((size_t)b * a.n_q + x) * kIdxDim;
-        const uint2 xv = *reinterpret_cast<const uint2 *>((DK ? a.k_idx : a.q_idx) + xo + 4 * lane);
-        float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, g3 = 0.0f;
-        for (int y = y_begin; y < lim; ++y) {
-            const int t = DK ? y : x, j = DK ? x : y;
-            if (DK && j >= row_limit(a, b, t)) continue;  // uniform
-            const size_t yo = DK ? ((size_t)b * a.n_q + y) * kIdxDim
-                                 : token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b, y, kIdxDim);
-            const uint2 yv = *reinterpret_cast<const uint2 *>((DK ? a.q_idx : a.k_idx) + yo + 4 * lane);
-            const float y0 = bf16_lo(yv.x), y1 = bf16_hi(yv.x), y2 = bf16_lo(yv.y), y3 = bf16_hi(yv.y);
-            const float c = wave_sum(fmaf(bf16_lo(xv.x), y0, bf16_hi(xv.x) * y1) +
-                                     fmaf(bf16_lo(xv.y), y2, bf16_hi(xv.y) * y3));
-            const size_t row = (size_t)b * a.n_q + t;
-            const float d = __builtin_amdgcn_exp2f(fmaf(c, kLossLog2e, -a.lse2[row])) -
-                            a.abar[row * a.max_len + j];
-            g0 = fmaf(d, y0, g0);
-            g1 = fmaf(d, y1, g1);
-            g2 = fmaf(d, y2, g2);
-            g3 = fmaf(d, y3, g3);
-        }
-        *reinterpret_cast<float4 *>(grad_dst<DK>(a, b, x, split) + 4 * lane) = make_float4(g0 * f, g1 * f, g2 * f, g3 * f);
-    }
-}
+// Not an infinity and not a NaN.
+__device__ __forceinline__ bool finite(float x) { return x - x == 0.0f; }
 
 // Gradient of one side.  DK false: own = rows, streamed = keys, out = dq, and
 // the rows' KL terms; true: own = keys, streamed = rows, out = dk.
@@ -397,11 +363,14 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
         if (n > 0) lse = a.lse2[(size_t)b * a.n_q + xi];
     }
     bf16x8 x[16];
-    if (DK)
-        load_own(a.k_idx + token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b,
-                                        min(xi, len - 1), kIdxDim), hi, x);
-    else
-        load_own(a.q_idx + ((size_t)b * a.n_q + min(xi, a.n_q - 1)) * kIdxDim, hi, x);
+    auto own_vectors = [&](int xi, int hi) {
+        if (DK)
+            load_own(a.k_idx + token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b,
+                                            min(xi, len - 1), kIdxDim), hi, x);
+        else
+            load_own(a.q_idx + ((size_t)b * a.n_q + min(xi, a.n_q - 1)) * kIdxDim, hi, x);
+    };
+    own_vectors(xi, hi);
     f32x16 acc[8];
 #pragma unroll
     for (int d = 0; d < 8; ++d)
@@ -464,7 +433,7 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
     };
     // Q - P of pairs e and e + 1 (e even) of half a tile, cut into three bf16
     // pieces, two pairs to a word
-    auto pieces2 = [&](int e, const f32x16 &c, const float (&p)[16], int lim, int kt, int buf,
+    auto pieces2 = [&](int e, int hi, float lse, const f32x16 &c, const float (&p)[16], int lim, int kt, int buf,
                        uint32_t (&pl)[3][8]) {
         uint32_t h[2], md[2], lo[2];
 #pragma unroll
@@ -497,12 +466,13 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
     const int ycol = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
     typedef __attribute__((address_space(3))) s16x4 lds4;
     bf16x8 v[4], w[4];  // operands read ahead
-    auto read_v = [&](bf16x8 &v, int buf, int kt, int kb, int d) {
+    auto read_at = [&](bf16x8 &v, int buf, int kt, int kb, int d, int yrow, int ycol) {
         const int yr = 32 * kt + 16 * kb + yrow;
         const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4 *)&s_y[buf][yr][32 * d + ycol]);
         const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4 *)&s_y[buf][yr + 8][32 * d + ycol]);
         v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
     };
+    auto read_v = [&](bf16x8 &v, int buf, int kt, int kb, int d) { read_at(v, buf, kt, kb, d, yrow, ycol); };
     auto read_w = [&](int buf, int kt, int ks) {
         w[ks & 3] = __builtin_bit_cast(
             bf16x8, *reinterpret_cast<const u32x4 *>(&s_y[buf][32 * kt + col][16 * ks + 8 * hi]));
@@ -532,7 +502,7 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
                                                                    pl[i][4 * kb + 2], pl[i][4 * kb + 3]});
                 acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[e & 3], pb, acc[d], 0, 0, 0);
             }
-            if ((e & 1) == 0) pieces2(e, co, po, lim, kt ^ 1, obuf, out);
+            if ((e & 1) == 0) pieces2(e, hi, lse, co, po, lim, kt ^ 1, obuf, out);
             c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[e & 3], x[e], c, 0, 0, 0);
             if (e & 1) __builtin_amdgcn_sched_barrier(0);
         }
@@ -550,7 +520,7 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
         tile_scores(s_y[0], 0, col, hi, x, c0);
         tile_scores(s_y[0], 1, col, hi, x, c1);
 #pragma unroll
-        for (int e = 0; e < 16; e += 2) pieces2(e, c0, p0, limit(start(0), true), 0, 0, pl0);
+        for (int e = 0; e < 16; e += 2) pieces2(e, hi, lse, c0, p0, limit(start(0), true), 0, 0, pl0);
 #pragma unroll
         for (int d = 0; d < 2; ++d) read_v(v[d], 0, 0, 0, d);
         int buf = 0;
@@ -577,14 +547,121 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
     const int own = DK ? len : a.n_q;
     if (x0 >= own) return;
     const float f = a.splits > 1 ? 1.0f : a.stats[0];
+    // A streamed value that is not finite reaches the products of own vectors that do
+    // not meet it (Q - P of zero does not remove it).  A wave with such a result makes
+    // it again, 32 streamed vectors at a time in its own sixth of the tiles (the loop's
+    // last barrier is behind every wave's last read): once the scores are made, values
+    // that are not finite become zeros there and are added by hand for the pairs that
+    // count.  8192 causal rows with one infinity 0.6 (a query) and 1.5 ms (a key), 0.4
+    // without; one pair at a time it was hundreds of times the usual.
     float odd = 0.0f;
 #pragma unroll
     for (int d = 0; d < 8; ++d)
 #pragma unroll
         for (int r = 0; r < 16; ++r) odd = fmaf(acc[d][r], 0.0f, odd);
-    if (__builtin_amdgcn_ballot_w64(odd != 0.0f)) {
-        kd_grad_exact<DK>(a, b, x0, own, y_begin, y_begin + a.span, f, split);
-        return;
+    if (__builtin_amdgcn_ballot_w64(odd != 0.0f && xi < own)) {
+        // the lane's place and its own vectors are made again: held over the loop for
+        // this they would spill
+        const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int col = lane & 31, hi = lane >> 5, xi = x0 + col;
+        const int n = DK ? 0 : row_limit(a, b, xi);
+        const float lse = n > 0 ? a.lse2[(size_t)b * a.n_q + xi] : 0.0f;
+        const int sb = wave >> 1, sk = wave & 1, last = DK ? a.n_q - 1 : wg_max - 1;
+        uint16_t(*slot)[kGrPitch] = &s_y[sb][32 * sk];
+        auto vector_at = [&](int yy) {
+            yy = min(yy, last);
+            return DK ? a.q_idx + ((size_t)b * a.n_q + yy) * kIdxDim
+                      : a.k_idx + token_offset(a.page_table, a.page_shift, a.max_pages, a.max_len, b, yy, kIdxDim);
+        };
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[d][r] = 0.0f;
+        own_vectors(xi, hi);
+        for (int h = 0; h < 2 * tiles; ++h) {
+            const int y0 = start(h >> 1) + 32 * (h & 1);
+            const int lim = DK ? xi : n - y0 + 32 * sk;
+#pragma unroll 4
+            for (int i = 0; i < 16; ++i)
+                *reinterpret_cast<u32x4 *>(&slot[2 * i + hi][col * 8]) =
+                    *reinterpret_cast<const u32x4 *>(vector_at(y0 + 2 * i + hi) + col * 8);
+            if (DK && lane < 32) {
+                s_lse[sb][32 * sk + lane] = a.lse2[(size_t)b * a.n_q + min(y0 + lane, last)];
+                s_n[sb][32 * sk + lane] = row_limit(a, b, y0 + lane);
+            }
+            __builtin_amdgcn_wave_barrier();
+            f32x16 c;
+            tile_scores(s_y[sb], sk, col, hi, x, c);
+            __builtin_amdgcn_wave_barrier();
+            uint32_t bad = 0u;  // streamed vectors with a value that is not finite
+#pragma unroll 1
+            for (int i = 0; i < 16; ++i) {
+                u32x4 v = *reinterpret_cast<const u32x4 *>(&slot[2 * i + hi][col * 8]);
+                bool some = false;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool lo = finite(bf16_lo(v[e])), up = finite(bf16_hi(v[e]));
+                    some |= !lo || !up;
+                    v[e] &= (lo ? 0x0000ffffu : 0u) | (up ? 0xffff0000u : 0u);
+                }
+                *reinterpret_cast<u32x4 *>(&slot[2 * i + hi][col * 8]) = v;
+                const uint64_t rows = __builtin_amdgcn_ballot_w64(some);
+                bad |= (((uint32_t)rows ? 1u : 0u) | ((uint32_t)(rows >> 32) ? 2u : 0u)) << (2 * i);
+            }
+            __builtin_amdgcn_wave_barrier();
+            float p[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int i = 8 * (e >> 2) + 4 * hi + (e & 3), yy = y0 + i;
+                const bool valid = DK ? xi < s_n[sb][32 * sk + i] : yy < n;
+                p[e] = valid ? a.abar[((size_t)b * a.n_q + (DK ? yy : xi)) * a.max_len + (DK ? xi : yy)] : 0.0f;
+            }
+            uint32_t pl[3][8];
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) pieces2(e, hi, lse, c, p, lim, sk, sb, pl);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    bf16x8 v;
+                    read_at(v, sb, sk, kb, d, 4 * hi + ((lane & 15) >> 2), 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+#pragma unroll
+                    for (int i = 2; i >= 0; --i)
+                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            v, __builtin_bit_cast(bf16x8, u32x4{pl[i][4 * kb], pl[i][4 * kb + 1],
+                                                                pl[i][4 * kb + 2], pl[i][4 * kb + 3]}),
+                            acc[d], 0, 0, 0);
+                }
+            __builtin_amdgcn_wave_barrier();
+            for (; bad; bad &= bad - 1u) {  // uniform
+                const int i = __builtin_ctz(bad);
+                const bool valid = DK ? xi < s_n[sb][32 * sk + i] : y0 + i < n;
+                // Q - P of vector i: pair 4 (i >> 3) + (i & 3) of lanes hi = (i >> 2) & 1
+                float q = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    float g = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) g += e & 1 ? bf16_hi(pl[k][e >> 1]) : bf16_lo(pl[k][e >> 1]);
+                    q = e == 4 * (i >> 3) + (i & 3) ? g : q;
+                }
+                const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(q), __float_as_uint(q), false, false);
+                const float qt = __uint_as_float(both[0]), qu = __uint_as_float(both[1]);
+                const uint16_t *yp = vector_at(y0 + i) + 4 * hi;
+#pragma unroll
+                for (int d = 0; d < 8; ++d)
+#pragma unroll
+                    for (int r = 0; r < 16; r += 4) {
+                        const uint2 w = *reinterpret_cast<const uint2 *>(yp + 32 * d + 2 * r);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const uint32_t word = k < 2 ? w.x : w.y;
+                            const float v = k & 1 ? bf16_hi(word) : bf16_lo(word);
+                            if (valid && !finite(v)) acc[d][r + k] = fmaf((i >> 2) & 1 ? qu : qt, v, acc[d][r + k]);
+                        }
+                    }
+            }
+        }
     }
     if (xi >= own) return;
     float *dst = grad_dst<DK>(a, b, xi, split);

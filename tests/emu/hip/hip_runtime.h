@@ -256,6 +256,8 @@ inline uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
 #define __builtin_amdgcn_sched_barrier(m) ((void)0)
 #define __builtin_amdgcn_wave_barrier emu::converge
 #define __builtin_amdgcn_perm emu::perm
+#define __builtin_amdgcn_mbcnt_lo(m, a) (a)
+#define __builtin_amdgcn_mbcnt_hi(m, a) ((int)(emu::thread_idx.x & 63))
 #define __builtin_amdgcn_exp2f exp2f
 #define __builtin_amdgcn_logf log2f
 #define __builtin_amdgcn_sbfe(v, o, w) ((int)((uint32_t)(v) << (32 - (w) - (o))) >> (32 - (w)))

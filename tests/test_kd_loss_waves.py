@@ -23,6 +23,7 @@ extern "C" void emu_kd(int batch, int n_q, int max_len, int page_shift, int max_
     clsa::launch_kd_loss(geometry(batch, n_q, max_len, page_shift, max_pages, causal), abar, q, k,
                          pt, sl, qp, loss, dq, dk, ws, nullptr);
 }
+extern "C" long emu_wave_ops() { return emu::wave_ops; }
 extern "C" size_t emu_kd_carved(int batch, int n_q, int max_len) {
     return clsa::kd_loss_plan(geometry(batch, n_q, max_len, -1, 0, 0)).floats;
 }
@@ -109,3 +110,47 @@ def test_carved_within_the_workspace(emu):
                             700, 1100, 4096, 33000, 262144):
                 have, need = emu.emu_kd_ws(batch, n_q, max_len), emu.emu_kd_carved(batch, n_q, max_len)
                 assert need <= have, (batch, n_q, max_len, need, have)
+
+
+def _float_model(w, x, abar):
+    """dq and dk in float64 from the pairs that count alone, every value as it is."""
+    q, k = (inputs.f32_from_bf16_bits(x[i]).astype(np.float64).reshape(-1, 256) for i in ("q_idx", "k_idx"))
+    if w.page_size:
+        row = (x["page_table"][0][:, None] * w.page_size + np.arange(w.page_size)).ravel()
+        k = k[row]
+    n = orc.valid_lens(orc.shape_of(w), x["seq_lens"], x["q_pos"])[0]
+    dq, dk = np.zeros(q.shape), np.zeros(k.shape)
+    with np.errstate(all="ignore"):
+        for t in range(w.n_q):
+            z = q[t] @ k[:n[t]].T
+            p = np.exp(z - z.max(initial=-np.inf))
+            d = (p / p.sum() - abar[0, t, :n[t]]) / max(1, int((n > 0).sum()))
+            dq[t] = (d[:, None] * k[:n[t]]).sum(0)
+            dk[:n[t]] += d[:, None] * q[t]
+    if w.page_size:
+        out = np.zeros(dk.shape)
+        out[row] = dk
+        dk = out
+    return dq.reshape(x["q_idx"].shape), dk.reshape(x["k_idx"].shape)
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("side,bad", [("q_idx", np.inf), ("q_idx", np.nan), ("k_idx", np.inf),
+                                      ("k_idx", np.nan), ("k_idx", -np.inf)])
+def test_values_not_finite(emu, side, bad, page):
+    """An index vector that is not finite reaches the gradients of the pairs it is in,
+    for at most a few times the work."""
+    w = inputs.small_workload(batch=1, lens=(144,), n_q=150, causal=True, q_pos0=(-6,), n_layers=1,
+                              page_size=page, q_heads=8, kv_heads=8, wid=105)
+    x, abar = _inputs(w)
+    _run(emu, w, x, abar)
+    usual = emu.emu_wave_ops()
+    x[side] = x[side].copy()
+    at = 70 if side == "q_idx" or not page else int(x["page_table"][0, 70 // page]) * page + 70 % page
+    x[side].reshape(-1, 256)[at, [3, 200]] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
+    _, dq, dk = _run(emu, w, x, abar)
+    assert emu.emu_wave_ops() <= 4 * usual
+    for got, ref in zip((dq, dk), _float_model(w, x, abar)):
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+        ok = np.isfinite(ref)
+        assert np.abs(got[ok] - ref[ok]).max(initial=0) <= 1e-5 * np.abs(ref[ok]).max(initial=0) + 1e-7
