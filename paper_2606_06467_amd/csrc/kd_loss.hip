@@ -376,7 +376,8 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
     for (int d = 0; d < 8; ++d)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[d][r] = 0.0f;
-    float kl = 0.0f;
+    // the row term by tiles, so that a long range is no chain of its length
+    float kl = 0.0f, total = 0.0f;
 
     // first vector of tile u (past the last: the last one again, nothing valid)
     auto start = [&](int u) {
@@ -534,6 +535,10 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
             step(pl0, 0, buf, nbuf, c0, c1, p1, limit(y0, true), buf, pl1, buf, 1);
             step(pl1, 1, buf, nbuf, c1, c0, p0, limit(y1, u + 1 < tiles), nbuf, pl0, nbuf, 0);
             stage(sbuf);
+            if (!DK) {
+                total += kl;
+                kl = 0.0f;
+            }
             __syncthreads();
             buf = nbuf;
 #pragma unroll
@@ -541,7 +546,7 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
         }
     }
     if (!DK) {
-        kl = both_sum(kl);
+        kl = both_sum(total + kl);
         if (hi == 0 && xi < a.n_q) a.row_kl[(size_t)split * a.rows + (size_t)b * a.n_q + xi] = kl * kLossLn2;
     }
     const int own = DK ? len : a.n_q;
@@ -682,7 +687,8 @@ __global__ __launch_bounds__(256) void kd_finish_rows_kernel(KdLossArgs a) {
     const int n = valid_keys(a.seq_lens, a.q_pos, a.causal, row / a.n_q, row, a.max_len);
     const int used = div_up(n, a.span);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    float kl = 0.0f;
+    // the row term by tiles, so that a long range is no chain of its length
+    float kl = 0.0f, total = 0.0f;
     for (int k = 0; k < used; ++k) {
         const float4 v = *reinterpret_cast<const float4 *>(a.part + ((size_t)k * a.rows + row) * kIdxDim + c);
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;

@@ -154,3 +154,18 @@ def test_values_not_finite(emu, side, bad, page):
         assert np.array_equal(np.isfinite(got), np.isfinite(ref))
         ok = np.isfinite(ref)
         assert np.abs(got[ok] - ref[ok]).max(initial=0) <= 1e-5 * np.abs(ref[ok]).max(initial=0) + 1e-7
+
+
+def test_row_term_of_equal_parts(emu):
+    """1000 equal terms a row, whose sum one after another in fp32 rounds the same way at
+    every step (500 a lane: an error of 6e-6): sums of 32 lose 32 + 16 roundings at most."""
+    w = inputs.small_workload(batch=1, lens=(1000,), n_q=1, n_layers=1, q_heads=8, kv_heads=8, wid=106)
+    x, abar = _inputs(w)
+    x["q_idx"] = np.zeros_like(x["q_idx"])
+    worst = 0.0
+    for p in np.float32([1.1171, 1.3701, 1.6117]):
+        abar[:] = p
+        loss, _, _ = _run(emu, w, x, abar)
+        exact = 1000 * float(p) * (np.log(float(p)) + np.log(1000.0))
+        worst = max(worst, abs(loss / exact - 1))
+    assert worst < 50 * 2.0 ** -25, worst
