@@ -447,7 +447,7 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
             if constexpr (!DK) {
                 // 0 log 0 = 0; the logarithm is clamped below 2^-126
                 const float t = __builtin_amdgcn_logf(fmaxf(pv, 0x1p-126f)) - z;
-                kl = fmaf(pv, pv > 0.0f ? t : 0.0f, kl);
+                kl = pv > 0.0f ? fmaf(pv, t, kl) : kl;
             }
             const float d = q - pv;
             h[k] = __float_as_uint(d) & 0xffff0000u;

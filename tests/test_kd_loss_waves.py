@@ -169,3 +169,17 @@ def test_row_term_of_equal_parts(emu):
         exact = 1000 * float(p) * (np.log(float(p)) + np.log(1000.0))
         worst = max(worst, abs(loss / exact - 1))
     assert worst < 50 * 2.0 ** -25, worst
+
+
+def test_target_not_a_number(emu):
+    """A target that is not a number has no term in the loss (only P > 0 has), and makes
+    the gradients of its row and key NaN."""
+    w = inputs.small_workload(batch=1, lens=(100,), n_q=3, n_layers=1, q_heads=8, kv_heads=8, wid=107)
+    x, abar = _inputs(w)
+    abar[0, 1, 70] = 0.0
+    without, _, _ = _run(emu, w, x, abar)
+    abar[0, 1, 70] = np.nan
+    loss, dq, dk = _run(emu, w, x, abar)
+    assert loss == without
+    assert np.isnan(dq[0, 1]).all() and np.isfinite(dq[0, [0, 2]]).all()
+    assert np.isnan(dk[0, 70]).all() and np.isfinite(np.delete(dk[0], 70, axis=0)).all()
