@@ -145,6 +145,8 @@ hipError_t launch_zero_u32(uint32_t *p, size_t n, hipStream_t stream);
 // ---- sparse_attn.hip ----
 // Partial buffer floats (0 when one split per (row, KV head)); dense: over max_len keys.
 size_t attn_partial_floats(const Geometry &g, bool dense = false);
+// Splits per (row, KV head) of the attention below.
+int attn_splits(const Geometry &g);
 // Attention gathering K/V rows from the cache through idx (and the page table).
 // split_done, if not null, is recorded right after the attention kernel, before
 // the split merge.  tickets: [rows, kv_heads] arrival counters, zero on entry and
@@ -189,8 +191,8 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
 // Chunked prefill as key tiles with a selection mask (a workspace of
 // scratch_floats words holds the mask): launch_attn_mask once per index set, then
 // launch_masked_attn per layer.  The index lists are ascending and hold every
-// position once.
-bool tile_attn_masked(const Geometry &g, size_t scratch_floats);
+// position once.  gather_splits: attn_splits(g).
+bool tile_attn_masked(const Geometry &g, size_t scratch_floats, int gather_splits);
 hipError_t launch_attn_mask(const Geometry &g, const int32_t *idx, const int32_t *n_sel,
                             const int32_t *seq_lens, uint32_t *mask, hipStream_t stream);
 hipError_t launch_masked_attn(const Geometry &g, const void *q, const void *k_cache,

@@ -663,6 +663,12 @@ size_t attn_partial_floats(const Geometry &g, bool dense) {
     return (size_t)g.rows * g.q_heads * splits * (kHeadDim + 2);
 }
 
+int attn_splits(const Geometry &g) {
+    int splits, cps;
+    plan_splits(g, g.top_k, false, splits, cps);
+    return splits;
+}
+
 size_t dense_partial_floats(const Geometry &g) {
     const size_t least = attn_partial_floats(g, true);
     if (!tile_attn_dense(g)) return least;

@@ -610,8 +610,12 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
 // priced with what they measured: a workgroup's tile step (8 waves x 64 keys, one
 // workgroup per CU) 3.1 us; a gather 22 + 1.4 G ps per (row, KV head, selected
 // token).  Per layer of 4096 rows x 16384 keys, k = 2048, 32 / 8 heads: gathers
-// 1.85 ms, tiles 1.2; 4096 x 32768: 1.95 against 2.6.
-bool tile_attn_masked(const Geometry &g, size_t scratch_floats) {
+// 1.85 ms, tiles 1.1; 4096 x 32768: 1.95 against 2.4.  Where the gathers need no
+// merge (one split), the mask's launch counts too: a step of 2 x 137 rows that select
+// everything, paged, 29.0 us in tiles and 25.9 gathered (priced 10.2 and 11.6), 2 x 122
+// rows, groups of 8 27.2 and 25.5 (6.8 and 8.3); with four splits 4 x 125 rows 27.5
+// and 48.2 (6.7 and 7.2).
+bool tile_attn_masked(const Geometry &g, size_t scratch_floats, int gather_splits) {
     if ((size_t)g.rows * mask_words(g) > scratch_floats) return false;
     if (g.n_q < kTileAttnMinRows) return false;
     const double wgs = (double)g.batch * tile_blocks(g) * g.kv_heads;
@@ -621,7 +625,7 @@ bool tile_attn_masked(const Geometry &g, size_t scratch_floats) {
     const double tiles_us = rounds * (keys / kTaKeys) * 3.1;
     const double sel = g.top_k < keys ? g.top_k : keys;
     const double gather_us = (double)g.rows * g.kv_heads * sel * (22.0 + 1.4 * g.group) * 1e-6;
-    return 1.1 * tiles_us < gather_us;
+    return 1.1 * tiles_us + (gather_splits > 1 ? 0.0 : 2.5) < gather_us;
 }
 
 hipError_t launch_attn_mask(const Geometry &g, const int32_t *idx, const int32_t *n_sel,

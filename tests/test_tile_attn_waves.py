@@ -22,6 +22,12 @@ extern "C" void emu_tile(int batch, int n_q, int max_len, int page_shift, int ma
     emu::wave_ops = 0;
     clsa::launch_tile_attn(g, q, k, v, pt, sl, qp, mask, splits, span, out, lse, po, pml, nullptr);
 }
+extern "C" int emu_masked(int batch, int n_q, int max_len, int top_k, int q_heads, int kv_heads,
+                           int splits) {
+    clsa::Geometry g{batch, n_q, batch * n_q, max_len, -1, 0, top_k, 1, q_heads, kv_heads,
+                     q_heads / kv_heads, 0.1f};
+    return clsa::tile_attn_masked(g, (size_t)1 << 40, splits);
+}
 extern "C" long emu_wave_ops() { return emu::wave_ops; }
 """
 
@@ -220,3 +226,14 @@ def test_values_not_finite(emu, bad, masked, page):
     _, ref_l = orc.sparse_attn(sh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, n,
                                x["page_table"])
     assert np.abs(lse - ref_l).max() < 1e-4
+
+
+@pytest.mark.parametrize("batch,n_q,n,k,qh,kvh,splits,tiles", [
+    (2, 137, 137, 512, 32, 8, 1, False), (2, 122, 122, 2048, 64, 8, 1, False),  # the mask's launch
+    (2, 138, 138, 1024, 64, 8, 1, True), (4, 125, 125, 1720, 20, 4, 4, True),   # ... and a merge
+    (1, 287, 287, 1024, 32, 8, 2, True), (4, 167, 167, 1024, 20, 4, 2, True),
+    (3, 473, 1674, 512, 32, 8, 2, True), (2, 2054, 5500, 512, 16, 8, 2, True),
+    (1, 179, 1002, 512, 32, 8, 2, False), (1, 4096, 32768, 2048, 32, 8, 8, False),  # few of the keys
+    (1, 15, 15, 512, 32, 8, 1, False)])
+def test_masked_tiles_where_they_measured_faster(emu, batch, n_q, n, k, qh, kvh, splits, tiles):
+    assert bool(emu.emu_masked(batch, n_q, n, k, qh, kvh, splits)) == tiles
