@@ -376,9 +376,9 @@ clsa_status decode_step_impl(const clsa_shape *shape, const void *q_idx, int64_t
     // emits the candidates (see topk.hip).
     const bool two_pass = clsa::topk_uses_two_pass(g);
     // Chunked prefill over few enough keys attends in key tiles with a selection
-    // mask; the mask takes the place of the split partials, which it needs none of.
-    const bool masked = n_layers > 0 && clsa::tile_attn_masked(g, clsa::attn_partial_floats(g), clsa::attn_splits(g));
-    uint32_t *mask = reinterpret_cast<uint32_t *>(w.partials);
+    // mask, which takes the place of the set's scores once its top-k is done.
+    const bool masked = n_layers > 0 && clsa::tile_attn_masked(g, clsa::attn_splits(g));
+    uint32_t *mask = reinterpret_cast<uint32_t *>(w.scores);
     const size_t q_stride = (size_t)g.rows * g.q_heads * 128;  // bf16 elements per layer
     const size_t lse_stride = (size_t)g.rows * g.q_heads;
     const size_t set_stride = (size_t)g.rows * g.top_k;         // index entries per set

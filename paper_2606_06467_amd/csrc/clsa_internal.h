@@ -188,11 +188,11 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
                             const int32_t *seq_lens, const int32_t *q_pos, const uint32_t *mask,
                             int splits, int span, void *out, float *lse, float *part_o,
                             float *part_ml, hipStream_t stream);
-// Chunked prefill as key tiles with a selection mask (a workspace of
-// scratch_floats words holds the mask): launch_attn_mask once per index set, then
+// Chunked prefill as key tiles with a selection mask (a word per 32 keys, which the
+// [rows, max_len] scores hold): launch_attn_mask once per index set, then
 // launch_masked_attn per layer.  The index lists are ascending and hold every
 // position once.  gather_splits: attn_splits(g).
-bool tile_attn_masked(const Geometry &g, size_t scratch_floats, int gather_splits);
+bool tile_attn_masked(const Geometry &g, int gather_splits);
 hipError_t launch_attn_mask(const Geometry &g, const int32_t *idx, const int32_t *n_sel,
                             const int32_t *seq_lens, uint32_t *mask, hipStream_t stream);
 hipError_t launch_masked_attn(const Geometry &g, const void *q, const void *k_cache,

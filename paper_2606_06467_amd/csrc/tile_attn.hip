@@ -614,10 +614,10 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
 // merge (one split), the mask's launch counts too: a step of 2 x 137 rows that select
 // everything, paged, 29.0 us in tiles and 25.9 gathered (priced 10.2 and 11.6), 2 x 122
 // rows, groups of 8 27.2 and 25.5 (6.8 and 8.3); with four splits 4 x 125 rows 27.5
-// and 48.2 (6.7 and 7.2).
-bool tile_attn_masked(const Geometry &g, size_t scratch_floats, int gather_splits) {
-    if ((size_t)g.rows * mask_words(g) > scratch_floats) return false;
-    if (g.n_q < kTileAttnMinRows) return false;
+// and 48.2 (6.7 and 7.2).  (Still a little in the tiles' favour for groups of 1: 4 x
+// 153 rows of which 243 keys a row 28.4 and 27.2.)
+bool tile_attn_masked(const Geometry &g, int gather_splits) {
+    if (g.n_q < kTileAttnMinRows || mask_words(g) > g.max_len) return false;  // the scores hold the mask
     const double wgs = (double)g.batch * tile_blocks(g) * g.kv_heads;
     const int half = g.max_len / 2, mean = g.max_len - g.n_q / 2;  // causal: the last n_q rows
     const double keys = wgs > 256 && g.causal ? (mean > half ? mean : half) : g.max_len;

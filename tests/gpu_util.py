@@ -5,6 +5,7 @@ Nothing here feeds a GPU result into the oracle: the oracle only ever sees the
 generator's arrays."""
 from __future__ import annotations
 
+import ctypes
 import os
 import sys
 import numpy as np
@@ -55,6 +56,40 @@ def shape_of(w, **over):
               page_size=w.page_size, max_pages=w.max_pages, causal=w.causal)
     kw.update(over)
     return B.make_shape(**kw)
+
+
+class _Geometry(ctypes.Structure):
+    """The library's own geometry (csrc/clsa_internal.h), to ask which path a shape takes."""
+    _fields_ = [(n, ctypes.c_int) for n in ("batch", "n_q", "rows", "max_len", "page_shift",
+                                            "max_pages", "top_k", "causal", "q_heads", "kv_heads",
+                                            "group")] + [("softmax_scale", ctypes.c_float)]
+
+
+def _ask(w, name, restype, *args):
+    from paper_2606_06467_amd import binding as B
+    g = _Geometry(w.batch, w.n_q, w.batch * w.n_q, w.max_len, w.page_size.bit_length() - 1,
+                  w.max_pages, w.top_k, int(w.causal), w.q_heads, w.kv_heads,
+                  w.q_heads // w.kv_heads, w.softmax_scale)
+    f = getattr(B.lib(), name)
+    f.restype = restype
+    return f(ctypes.byref(g), *args)
+
+
+def dense_in_tiles(w) -> bool:
+    return _ask(w, "_ZN4clsa15tile_attn_denseERKNS_8GeometryE", ctypes.c_bool)
+
+
+def step_in_tiles(w) -> bool:
+    """Whether the layers of a step attend in key tiles with a selection mask."""
+    splits = _ask(w, "_ZN4clsa11attn_splitsERKNS_8GeometryE", ctypes.c_int)
+    return _ask(w, "_ZN4clsa16tile_attn_maskedERKNS_8GeometryEi", ctypes.c_bool, ctypes.c_int(splits))
+
+
+def least_dense_workspace(w) -> int:
+    """Bytes that clsa_dense_attn needs at least (clsa_workspace_bytes may say more)."""
+    n = 4 * _ask(w, "_ZN4clsa19attn_partial_floatsERKNS_8GeometryEb", ctypes.c_size_t,
+                 ctypes.c_bool(True))
+    return -(-n // 256) * 256
 
 
 def higham_bound(w, x) -> np.ndarray:

@@ -24,6 +24,7 @@ def test_tile_edges(nq, n, ps, qh, kvh):
     w = inputs.small_workload(batch=3, lens=(n, nq // 2, 0), n_q=nq, causal=True,
                               q_pos0=(n - nq, nq // 2 - nq, -nq), q_heads=qh, kv_heads=kvh,
                               page_size=ps, n_layers=1, wid=81)
+    assert U.dense_in_tiles(w)
     _case(w, f"tiles {nq} rows {n} keys Hq={qh} Hkv={kvh} page={ps}")
 
 
@@ -95,6 +96,7 @@ def test_step_with_selection_masks(qh, kvh, ps, top_k):
     w = inputs.small_workload(batch=2, lens=(1000, 610), n_q=1000, causal=True,
                               q_pos0=(0, 610 - 1000), q_heads=qh, kv_heads=kvh, page_size=ps,
                               top_k=top_k, n_layers=2, wid=85)
+    assert U.step_in_tiles(w)
     _check_step(w, inputs.make_inputs(w), [1], f"masked tiles k={top_k} Hq={qh} Hkv={kvh}")
 
 
@@ -104,6 +106,7 @@ def test_step_selection_excludes_values_not_finite(ps):
     from tests.test_gpu_decode_step import _gpu_step
     w = inputs.small_workload(batch=1, lens=(960,), n_q=960, causal=True, q_pos0=(0,), top_k=400,
                               page_size=ps, n_layers=1, wid=86)
+    assert U.step_in_tiles(w)
     x = inputs.make_inputs(w)
     at = (int(x["page_table"][0, 500 // ps]), 500 % ps) if ps else (0, 500)
     x["v_cache"][at][:, 7] = inputs.bf16_bits_from_f32(np.float32([np.inf]))[0]
@@ -149,3 +152,53 @@ def test_scale_not_positive(scale):
         ref_o, ref_l = orc.sparse_attn(osh, x["q_layers"][0], x["k_cache"], x["v_cache"], idx, ns)
         U.compare_attn(B.bits_from_bf16(out[0]), lse[0].cpu().numpy().astype(np.float64), ref_o,
                        ref_l, what=f"scale {scale}, {nq} rows")
+
+
+@pytest.mark.parametrize("top_k", [300, 700])
+def test_masked_step_grouped_and_replayed(top_k):
+    """The mask lies in the scores of its index set: sets made afresh for every layer
+    give the shared step's results, and so does every replay of a captured step."""
+    import torch
+    from paper_2606_06467_amd import binding as B
+    w = inputs.small_workload(batch=2, lens=(1000, 410), n_q=600, causal=True,
+                              q_pos0=(400, 410 - 600), top_k=top_k, n_layers=3, wid=93)
+    assert U.step_in_tiles(w)
+    d = U.to_dev(inputs.make_inputs(w))
+    sh, q = U.shape_of(w), d["q_layers"]
+    ws = B.workspace(sh, B.CLSA_OP_DECODE, 3)
+
+    def outputs(sets):
+        return (torch.empty(q.shape, dtype=torch.bfloat16, device="cuda"),
+                torch.empty(q.shape[:-1], device="cuda"),
+                torch.empty((sets, 2, 600, top_k), dtype=torch.int32, device="cuda"),
+                torch.empty((sets, 2, 600), dtype=torch.int32, device="cuda"))
+
+    def shared(o):
+        B.clsa_decode_step(sh, d["q_idx"], d["k_idx"], d["k_cache"], d["v_cache"], None,
+                           d["seq_lens"], d["q_pos"], q, *o, ws)
+
+    def same(a, b):
+        return all(torch.equal(x.view(torch.int16) if x.dtype == torch.bfloat16 else x,
+                               y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
+                   for x, y in zip(a, b))
+
+    ref = outputs(1)
+    shared(ref)
+    got = outputs(3)
+    B.clsa_decode_step_grouped(sh, d["q_idx"], 0, d["k_idx"], 0, d["k_cache"], d["v_cache"], None,
+                               d["seq_lens"], d["q_pos"], 1, q, *got, ws)
+    torch.cuda.synchronize()
+    assert same(got[:2], ref[:2])
+    assert all(torch.equal(got[2][s], ref[2][0]) and torch.equal(got[3][s], ref[3][0]) for s in range(3))
+    rep = outputs(1)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        shared(rep)
+    for _ in range(3):
+        for t in rep:
+            t.fill_(0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert same(rep, ref)
+        shared(outputs(1))  # eager work between replays
+        torch.cuda.synchronize()

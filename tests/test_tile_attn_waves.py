@@ -22,11 +22,16 @@ extern "C" void emu_tile(int batch, int n_q, int max_len, int page_shift, int ma
     emu::wave_ops = 0;
     clsa::launch_tile_attn(g, q, k, v, pt, sl, qp, mask, splits, span, out, lse, po, pml, nullptr);
 }
+extern "C" void emu_mask(int batch, int n_q, int max_len, int top_k, const int32_t *idx,
+                         const int32_t *n_sel, const int32_t *sl, uint32_t *mask) {
+    clsa::Geometry g{batch, n_q, batch * n_q, max_len, -1, 0, top_k, 1, 8, 8, 1, 0.1f};
+    clsa::launch_attn_mask(g, idx, n_sel, sl, mask, nullptr);
+}
 extern "C" int emu_masked(int batch, int n_q, int max_len, int top_k, int q_heads, int kv_heads,
                            int splits) {
     clsa::Geometry g{batch, n_q, batch * n_q, max_len, -1, 0, top_k, 1, q_heads, kv_heads,
                      q_heads / kv_heads, 0.1f};
-    return clsa::tile_attn_masked(g, (size_t)1 << 40, splits);
+    return clsa::tile_attn_masked(g, splits);
 }
 extern "C" long emu_wave_ops() { return emu::wave_ops; }
 """
@@ -237,3 +242,24 @@ def test_values_not_finite(emu, bad, masked, page):
     (1, 15, 15, 512, 32, 8, 1, False)])
 def test_masked_tiles_where_they_measured_faster(emu, batch, n_q, n, k, qh, kvh, splits, tiles):
     assert bool(emu.emu_masked(batch, n_q, n, k, qh, kvh, splits)) == tiles
+
+
+def test_mask_of_long_rows(emu):
+    """Rows of more than 65536 keys take several passes: runs of entries that cross a
+    pass, entries in one pass alone, none; nothing is written past a sequence's words."""
+    max_len, k = 140000, 3000
+    g = np.random.default_rng(5)
+    lens = np.array([140000, 70001], np.int32)
+    rows = [np.sort(g.choice(140000, 3000, replace=False)), np.arange(64000, 67000),
+            np.sort(g.choice(70001, 700, replace=False)), np.arange(65530, 65545)[:0],
+            np.arange(66000, 66100), np.array([0, 31, 32, 65535, 65536, 70000])]
+    idx, n = np.full((2, 3, k), -1, np.int32), np.zeros((2, 3), np.int32)
+    for r, s in zip(np.ndindex(2, 3), (rows[0], rows[1], rows[5], rows[2], rows[3], rows[4])):
+        idx[r][:s.size], n[r] = s, s.size
+    words = 2 * -(-max_len // 64)
+    mask = np.full((2, 3, words), 0xabcdabcd, np.uint32)
+    emu.emu_mask(2, 3, max_len, k, _p(idx), _p(n), _p(lens), _p(mask))
+    ref = _mask(idx, n, max_len)
+    used = 2 * -(-70001 // 64)
+    assert np.array_equal(mask[0], ref[0]) and np.array_equal(mask[1, :, :used], ref[1, :, :used])
+    assert (mask[1, :, used:] == 0xabcdabcd).all()
