@@ -21,7 +21,7 @@ def _full_sets(w, seq_lens, q_pos):
     return sh, idx, n.astype(np.int32)
 
 
-def _case(w, what):
+def _case(w, what, ws_bytes=None):
     import torch
     from paper_2606_06467_amd import binding as B
     x = inputs.make_inputs(w, layers=[0])
@@ -31,6 +31,8 @@ def _case(w, what):
     lse = torch.full(q.shape[:-1], float("nan"), device="cuda")
     sh = U.shape_of(w)
     ws = B.workspace(sh, B.CLSA_OP_DENSE)
+    if ws_bytes is not None:
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
     B.clsa_dense_attn(sh, q, d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"],
                       d["q_pos"], out, lse, ws)
     torch.cuda.synchronize()
@@ -61,9 +63,9 @@ def test_causal_rows():
 
 @pytest.mark.parametrize("qh,kvh,nq,ps", [(8, 8, 520, 0), (32, 8, 520, 64), (20, 4, 1030, 0)])
 def test_many_rows_split_by_key_range(qh, kvh, nq, ps):
-    """Dense attention over 4096+ (row, KV head) units (the one-wave chunked-prefill
-    form with its rotated chunk order), split by key range: groups of 1, 4 and 5
-    heads, contiguous and paged caches."""
+    """Dense attention of many rows per sequence, 4096+ (row, KV head) units: key tiles
+    shared by a block of rows, for groups of 1, 4 and 5 heads, contiguous and paged
+    caches (the per-row kernel's form for as many units: test_many_units_of_few_rows)."""
     w = inputs.small_workload(batch=1, lens=(1500,), n_q=nq, causal=True, q_pos0=(1500 - nq,),
                               q_heads=qh, kv_heads=kvh, page_size=ps, n_layers=1, wid=75)
     _case(w, f"dense {nq} causal rows Hq={qh} Hkv={kvh} page={ps}")
@@ -78,3 +80,31 @@ def test_many_splits_one_row():
 def test_full_size_128k():
     w = inputs.workload("decode_b4_n128k_planted")
     _case(w, "dense decode_b4_n128k_planted")
+
+
+@pytest.mark.parametrize("qh,kvh,ps", [(8, 8, 0), (32, 8, 64), (20, 4, 0), (64, 8, 16)])
+def test_many_units_of_few_rows(qh, kvh, ps):
+    """4096 or more (row, KV head) units of fewer rows per sequence than the key tiles
+    take: the one-wave form of the per-row kernel over two key ranges, with its rotated
+    chunk order, for groups of 1, 4, 5 and 8 heads."""
+    batch = 4096 // (8 * kvh)
+    w = inputs.small_workload(batch=batch, lens=tuple(520 - 7 * (b % 70) for b in range(batch)), n_q=8,
+                              causal=True, q_pos0=tuple(512 - 7 * (b % 70) for b in range(batch)),
+                              q_heads=qh, kv_heads=kvh, page_size=ps, n_layers=1, wid=76)
+    assert w.batch * w.n_q * kvh >= 4096 and not U.dense_in_tiles(w)
+    assert U.least_dense_workspace(w) > 0  # more than one key range
+    _case(w, f"dense {batch} x 8 rows Hq={qh} Hkv={kvh} page={ps}")
+
+
+@pytest.mark.parametrize("nq,n,ps", [(16, 5000, 0), (40, 3000, 64)])
+def test_least_workspace(nq, n, ps):
+    """Many rows in a workspace that holds the per-row kernel's partials only, or one
+    byte less than the tiles' own: the per-row kernel serves them."""
+    w = inputs.small_workload(batch=1, lens=(n,), n_q=nq, causal=True, q_pos0=(n - nq,),
+                              page_size=ps, n_layers=1, wid=77)
+    from paper_2606_06467_amd import binding as B
+    full = B.clsa_workspace_bytes(U.shape_of(w), B.CLSA_OP_DENSE)
+    least = U.least_dense_workspace(w)
+    assert U.dense_in_tiles(w) and 0 < least < full
+    for n_bytes in (least, full - 256, full):
+        _case(w, f"dense {nq} x {n}, {n_bytes} bytes of workspace", ws_bytes=n_bytes)
