@@ -31,10 +31,9 @@ __device__ __forceinline__ float dot8_bf16(uint4 a, uint4 b, float acc) {
 
 // Lane exchanges without the LDS crossbar.  Inside a row of 16 lanes, DPP (a
 // VALU operand modifier): lane i reads lane 15 - i (row mirror), 7 - i within
-// its half-row (half mirror), i ^ 2 or i ^ 1 (quad permutes).  Across rows,
-// the gfx950 permlane swaps: v_permlane32_swap(x, y) leaves lanes 0-31 with
-// (x[i], x[i + 32]) and lanes 32-63 with (y[i - 32], y[i]); v_permlane16_swap
-// does the same between rows 0 and 1 and between rows 2 and 3.
+// its half-row (half mirror), i ^ 2 or i ^ 1 (quad permutes).  Across rows, the
+// gfx950 permlane swaps: v_permlane16_swap(x, y) leaves the lanes of rows 0 and 2
+// with (x[i], x[i + 16]) and those of rows 1 and 3 with (y[i - 16], y[i]).
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, false));
@@ -52,86 +51,33 @@ __device__ __forceinline__ float row_partner(float x) {
     else return dpp_f32<0xB1>(x);
 }
 
-// lo + partner's lo for lanes with bit M clear, hi + partner's hi for lanes with
-// it set (M = 16 or 32): the exchange step across rows.
-template <int M>
-__device__ __forceinline__ float cross_row_step(float lo, float hi) {
-    static_assert(M == 16 || M == 32, "across rows");
-    const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(lo),
-                                                              __float_as_uint(hi), false, false)
-                           : __builtin_amdgcn_permlane16_swap(__float_as_uint(lo),
-                                                              __float_as_uint(hi), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Transpose-reduction across lanes.  Each lane holds CNT partial values; at the
-// exchange with its partner at distance M it keeps the half selected by
-// (lane & M) and adds the partner's copy of that half, for M, M/2, ..., MSTOP.
-// Once a single value is left the remaining exchanges are plain sums.  With
-// CNT = 2^s values and s halving steps, lane L ends with value index (L's step
-// bits, high to low) of the original CNT, summed over every lane the steps
-// visited.  All sizes are compile-time so that every register index stays static.
-template <int CNT, int M, int MSTOP, int NV>
-__device__ __forceinline__ void transpose_reduce(float (&p)[NV], int lane) {
-    if constexpr (M >= MSTOP) {
-        if constexpr (CNT > 1) {
-            constexpr int H = CNT / 2;
-            if constexpr (M >= 16) {
+// Transpose-reduction over the 32 lanes that share a value of bit 5.  Each lane
+// holds 16 partial values; at the exchange with its partner at distance M = 16, 8,
+// 4 and 2 it keeps the half of its values selected by (lane & M) and adds the
+// partner's copy of that half, and the last exchange (M = 1) is a plain sum: lane L
+// ends with value index (L >> 1) & 15 in p[0], summed over the 32 lanes.  All sizes
+// are compile-time so that every register index stays static.
+template <int CNT = 16, int M = 16>
+__device__ __forceinline__ void transpose_reduce(float (&p)[16], int lane) {
+    if constexpr (CNT == 1) {
+        p[0] += row_partner<M>(p[0]);
+    } else {
+        constexpr int H = CNT / 2;
 #pragma unroll
-                for (int v = 0; v < H; ++v) p[v] = cross_row_step<M>(p[v], p[v + H]);
+        for (int v = 0; v < H; ++v) {
+            if constexpr (M == 16) {
+                const auto r = __builtin_amdgcn_permlane16_swap(
+                    __float_as_uint(p[v]), __float_as_uint(p[v + H]), false, false);
+                p[v] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
             } else {
                 const bool up = (lane & M) != 0;
-#pragma unroll
-                for (int v = 0; v < H; ++v) {
-                    const float keep = up ? p[v + H] : p[v];
-                    const float send = up ? p[v] : p[v + H];
-                    p[v] = keep + row_partner<M>(send);
-                }
+                const float keep = up ? p[v + H] : p[v];
+                const float send = up ? p[v] : p[v + H];
+                p[v] = keep + row_partner<M>(send);
             }
-            transpose_reduce<H, M / 2, MSTOP, NV>(p, lane);
-        } else {
-            if constexpr (M >= 16) p[0] = cross_row_step<M>(p[0], p[0]);
-            else p[0] += row_partner<M>(p[0]);
-            transpose_reduce<1, M / 2, MSTOP, NV>(p, lane);
         }
+        transpose_reduce<H, M / 2>(p, lane);
     }
-}
-
-// Maximum / sum over the 16 lanes of this lane's row; every lane of the row
-// gets the result (quad swaps, then the half and full row mirrors).
-__device__ __forceinline__ float row16_max(float x) {
-    x = fmaxf(x, dpp_f32<0xB1>(x));
-    x = fmaxf(x, dpp_f32<0x4E>(x));
-    x = fmaxf(x, dpp_f32<0x141>(x));
-    return fmaxf(x, dpp_f32<0x140>(x));
-}
-__device__ __forceinline__ float row16_sum(float x) {
-    x += dpp_f32<0xB1>(x);
-    x += dpp_f32<0x4E>(x);
-    x += dpp_f32<0x141>(x);
-    return x + dpp_f32<0x140>(x);
-}
-
-// Maximum / sum over all 64 lanes; every lane gets the result.
-__device__ __forceinline__ float wave_max(float x) {
-    x = fmaxf(x, dpp_f32<0xB1>(x));
-    x = fmaxf(x, dpp_f32<0x4E>(x));
-    x = fmaxf(x, dpp_f32<0x141>(x));
-    x = fmaxf(x, dpp_f32<0x140>(x));
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float wave_sum(float x) {
-    x += dpp_f32<0xB1>(x);
-    x += dpp_f32<0x4E>(x);
-    x += dpp_f32<0x141>(x);
-    x += dpp_f32<0x140>(x);
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }

@@ -71,7 +71,7 @@ __device__ __forceinline__ void index_tile(const IndexArgs &a, int row, int b, i
     // halving exchanges (lane ^ 16, 8, 4, 2) lane `sub` holds token slot
     // sub >> 1 summed over 16 lanes, and the exchange with lane ^ 1 completes
     // the sum over all 32.
-    transpose_reduce<16, 16, 1, 16>(p, sub);
+    transpose_reduce(p, sub);
 
     const int slot = (sub >> 1) & 15;
     const int tok = tok0 + 2 * slot + half;
