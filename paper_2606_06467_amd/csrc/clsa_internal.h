@@ -167,19 +167,22 @@ hipError_t launch_dense_attn(const Geometry &g, const void *q, const void *k_cac
 // enough; with dense_partial_floats(g), many rows over few row blocks split their
 // keys over enough workgroups to fill the chip.
 size_t dense_partial_floats(const Geometry &g);
+// Whether dense attention runs over key tiles (given dense_partial_floats(g)).
+bool dense_in_tiles(const Geometry &g);
 
 // ---- tile_attn.hip ----
 // Dense attention runs over key tiles shared by a block of rows from 16 query
 // rows per sequence (half of a block's 32; against one gather per row, 32 / 8
 // heads: 16 rows x 32768 keys 48 us against 112, 8 sequences of 4096 keys 49
 // against 100, 2000 keys 14 each way) and 4e5 keys over all (row, KV head) pairs
-// (64 rows x 600 keys x 8: 3.1e5, 18.1 us against 15.1; 32 x 2000 x 8: 5.1e5, 16.4
-// against 17.3; 500 x 600 x 8: 2.4e6, 25 against 38).  Workgroups aimed at (by
-// splitting the key range): one per CU.
+// (64 rows x 600 keys x 8: 3.1e5, 20.0 us against 14.6), where their price is below
+// the gathers' (tile_attn_dense; gather_splits: the per-row kernel's key ranges).
+// Workgroups aimed at (by splitting the key range): one per CU.
 constexpr int kTileAttnMinRows = 16;
 constexpr double kTileAttnMinKeys = 4e5;
 constexpr int kTileAttnWorkgroups = 256;
-bool tile_attn_dense(const Geometry &g);
+bool tile_attn_dense(const Geometry &g, int gather_splits);
+constexpr int kMaxSplits = 128;  // key ranges per (row, KV head): the merge's largest shape
 // Key ranges per row (at most max_splits) and keys per range.
 void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span);
 // mask: null, or the selection mask.  Partials as in sparse_attn.hip when splits > 1.

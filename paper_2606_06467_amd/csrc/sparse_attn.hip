@@ -49,7 +49,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kHeadDim = 128;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kMaxSplits = 128;  // splits per (row, KV head): the merge's largest shape
 constexpr int kManyUnits = 4096; // (row, KV head) units from which splits go by key range
 constexpr int kKtPitch = 17;     // 16-byte pieces per staged K row (one of padding)
 constexpr int kManySplits = 8;   // splits per unit then (measured best of 1, 2, 4, 8, 16)
@@ -669,9 +668,15 @@ int attn_splits(const Geometry &g) {
     return splits;
 }
 
+bool dense_in_tiles(const Geometry &g) {
+    int splits, cps;
+    plan_splits(g, g.max_len, true, splits, cps);
+    return tile_attn_dense(g, splits);
+}
+
 size_t dense_partial_floats(const Geometry &g) {
     const size_t least = attn_partial_floats(g, true);
-    if (!tile_attn_dense(g)) return least;
+    if (!dense_in_tiles(g)) return least;
     int splits, span;
     tile_attn_plan(g, kMaxSplits, splits, span);
     if (splits == 1) return least;
@@ -781,7 +786,7 @@ hipError_t launch_dense_attn(const Geometry &g, const void *q, const void *k_cac
     a.q_pos = q_pos;
     if (g.rows == 0) return hipSuccess;
     const int units = g.rows * g.q_heads;
-    if (tile_attn_dense(g)) {
+    if (dense_in_tiles(g)) {
         int splits, span;
         tile_attn_plan(g, kMaxSplits, splits, span);
         const size_t slots = (size_t)g.rows * g.q_heads * splits;

@@ -537,11 +537,6 @@ __global__ __launch_bounds__(kMaskThreads) void attn_mask_kernel(MaskArgs a) {
 constexpr int kTaWaves = 8;
 static int tile_blocks(const Geometry &g) { return div_up(div_up(g.n_q, 32) * g.group, kTaWaves); }
 
-bool tile_attn_dense(const Geometry &g) {
-    return g.n_q >= kTileAttnMinRows &&
-           (double)g.rows * g.kv_heads * g.max_len >= kTileAttnMinKeys;
-}
-
 void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span) {
     const long blocks = (long)g.batch * tile_blocks(g) * g.kv_heads;
     long want = (kTileAttnWorkgroups + blocks - 1) / blocks;
@@ -551,6 +546,35 @@ void tile_attn_plan(const Geometry &g, int max_splits, int &splits, int &span) {
     if (want < 1) want = 1;
     span = div_up(tiles, (int)want) * kTaKeys;
     splits = div_up(g.max_len, span);
+}
+
+// Keys a row has on average, where every sequence is full (causal: the last n_q rows).
+static double mean_keys(const Geometry &g) {
+    const int half = g.max_len / 2, mean = g.max_len - g.n_q / 2;
+    return !g.causal ? g.max_len : mean > half ? mean : half;
+}
+
+// Both sides priced in us with what 3850 shapes measured (16 to 1100 rows, 130 to
+// 40000 keys, groups of 1 to 8, contiguous and paged).  Tiles: 3.2 more to start and
+// end than gathers, 1.9 a tile and round of the chip, 0.6 a MB of range partials;
+// gathers: 17 + 0.75 G ps per (row, KV head, key), 2.5 for the merge and 0.4 a MB of
+// partials.  Many query heads over few keys make the tiles' partials large: 4 x 32
+// rows x 600 keys, 64 / 8 heads 19.4 us gathered and 33.8 in tiles (by the limits
+// alone they were taken), 500 rows x 600 causal keys, 20 / 4 heads 24 and 31, 32 / 8
+// 37 and 32 (the price is still wrong here), 3 x 500 x 600 64 / 8 151 and 42.
+bool tile_attn_dense(const Geometry &g, int gather_splits) {
+    if (g.n_q < kTileAttnMinRows || (double)g.rows * g.kv_heads * g.max_len < kTileAttnMinKeys)
+        return false;
+    int splits, span;
+    tile_attn_plan(g, kMaxSplits, splits, span);
+    const double wgs = (double)g.batch * tile_blocks(g) * g.kv_heads * splits;
+    const double keys = mean_keys(g), rounds = ceil(wgs / kTileAttnWorkgroups);
+    const double split_mb = (double)g.rows * g.q_heads * (kTaDim + 2) * sizeof(float) * 1e-6;
+    const double tiles_us = 3.2 + rounds * (span < keys ? span : keys) / kTaKeys * 1.9 +
+                            (splits > 1 ? 0.6 * split_mb * splits : 0.0);
+    const double gather_us = (double)g.rows * g.kv_heads * keys * (17.0 + 0.75 * g.group) * 1e-6 +
+                             (gather_splits > 1 ? 2.5 + 0.4 * split_mb * gather_splits : 0.0);
+    return tiles_us < gather_us;
 }
 
 static int mask_words(const Geometry &g) { return div_up(g.max_len, kTaKeys) * (kTaKeys / 32); }
@@ -619,8 +643,7 @@ hipError_t launch_tile_attn(const Geometry &g, const void *q, const void *k_cach
 bool tile_attn_masked(const Geometry &g, int gather_splits) {
     if (g.n_q < kTileAttnMinRows || mask_words(g) > g.max_len) return false;  // the scores hold the mask
     const double wgs = (double)g.batch * tile_blocks(g) * g.kv_heads;
-    const int half = g.max_len / 2, mean = g.max_len - g.n_q / 2;  // causal: the last n_q rows
-    const double keys = wgs > 256 && g.causal ? (mean > half ? mean : half) : g.max_len;
+    const double keys = wgs > 256 ? mean_keys(g) : g.max_len;
     const double rounds = wgs > 256 ? wgs / 256 + 0.3 : 1.0;  // the last round is partly empty
     const double tiles_us = rounds * (keys / kTaKeys) * 3.1;
     const double sel = g.top_k < keys ? g.top_k : keys;

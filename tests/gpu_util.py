@@ -76,7 +76,7 @@ def _ask(w, name, restype, *args):
 
 
 def dense_in_tiles(w) -> bool:
-    return _ask(w, "_ZN4clsa15tile_attn_denseERKNS_8GeometryE", ctypes.c_bool)
+    return _ask(w, "_ZN4clsa14dense_in_tilesERKNS_8GeometryE", ctypes.c_bool)
 
 
 def step_in_tiles(w) -> bool:

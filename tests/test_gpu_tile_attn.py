@@ -14,16 +14,19 @@ from tests.test_gpu_dense import _case, _full_sets
 pytestmark = pytest.mark.gpu
 
 
-# at least 4e5 keys over all (row, KV head) pairs, so that the tiles are taken
 @pytest.mark.parametrize("nq,n,ps", [(17, 4161, 0), (32, 2113, 16), (33, 2048, 0), (97, 769, 64),
                                      (250, 321, 0), (288, 288, 64)])
 @pytest.mark.parametrize("qh,kvh", [(4, 4), (4, 2), (32, 8), (10, 2), (16, 2)])
 def test_tile_edges(nq, n, ps, qh, kvh):
     """Causal rows that end with their sequence; the second sequence is shorter
-    than the block of rows (its first rows see nothing), the third is empty."""
-    w = inputs.small_workload(batch=3, lens=(n, nq // 2, 0), n_q=nq, causal=True,
-                              q_pos0=(n - nq, nq // 2 - nq, -nq), q_heads=qh, kv_heads=kvh,
-                              page_size=ps, n_layers=1, wid=81)
+    than the block of rows (its first rows see nothing), the third is empty.  As often
+    as it takes for the tiles to be chosen."""
+    for times in (1, 2, 4, 8, 16):
+        w = inputs.small_workload(batch=3 * times, lens=(n, nq // 2, 0) * times, n_q=nq, causal=True,
+                                  q_pos0=(n - nq, nq // 2 - nq, -nq) * times, q_heads=qh,
+                                  kv_heads=kvh, page_size=ps, n_layers=1, wid=81)
+        if U.dense_in_tiles(w):
+            break
     assert U.dense_in_tiles(w)
     _case(w, f"tiles {nq} rows {n} keys Hq={qh} Hkv={kvh} page={ps}")
 
@@ -32,6 +35,7 @@ def test_tile_edges(nq, n, ps, qh, kvh):
 def test_not_causal_split_by_key_range(nq, n):
     """Few row blocks: the key range is split and merged; every row sees every key."""
     w = inputs.small_workload(batch=2, lens=(n, n // 3), n_q=nq, n_layers=1, wid=82)
+    assert U.dense_in_tiles(w)
     _case(w, f"tiles {nq} rows {n} keys, split")
 
 
@@ -39,6 +43,7 @@ def test_large_logits():
     """Logits of hundreds: the running maximum moves far, in both directions."""
     w = inputs.small_workload(batch=1, lens=(1300,), n_q=40, causal=True, q_pos0=(1260,),
                               n_layers=1, wid=83)
+    assert U.dense_in_tiles(w)
     x = inputs.make_inputs(w, layers=[0])
     k = inputs.f32_from_bf16_bits(x["k_cache"])
     k *= np.linspace(-30, 30, 1300)[None, :, None, None]
@@ -70,14 +75,15 @@ def _run_and_compare(w, x, mask_rows=None):
 @pytest.mark.parametrize("which", ["k_cache", "v_cache"])
 def test_values_not_finite_stay_with_the_rows_that_see_them(which, bad):
     """A token whose key or value is not finite changes no row before it."""
-    w = inputs.small_workload(batch=1, lens=(800,), n_q=70, causal=True, q_pos0=(730,),
+    w = inputs.small_workload(batch=1, lens=(1500,), n_q=70, causal=True, q_pos0=(1430,),
                               n_layers=1, wid=84)
+    assert U.dense_in_tiles(w)
     x = inputs.make_inputs(w, layers=[0])
     x["k_cache"] = x["k_cache"].copy()
     x["v_cache"] = x["v_cache"].copy()
-    x[which][0, 750, :, 5] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
+    x[which][0, 1450, :, 5] = inputs.bf16_bits_from_f32(np.float32([bad]))[0]
     before = np.zeros((1, 70), bool)
-    before[0, :20] = True  # positions 730 .. 749
+    before[0, :20] = True  # positions 1430 .. 1449
     o, ls = _run_and_compare(w, x, mask_rows=before)
     if which == "v_cache":  # the others carry it, in that dimension alone
         assert not np.isfinite(o[0, 20:, :, 5]).any()

@@ -33,6 +33,11 @@ extern "C" int emu_masked(int batch, int n_q, int max_len, int top_k, int q_head
                      q_heads / kv_heads, 0.1f};
     return clsa::tile_attn_masked(g, splits);
 }
+extern "C" int emu_dense(int batch, int n_q, int max_len, int causal, int q_heads, int kv_heads, int splits) {
+    clsa::Geometry g{batch, n_q, batch * n_q, max_len, -1, 0, 1, causal, q_heads, kv_heads,
+                     q_heads / kv_heads, 0.1f};
+    return clsa::tile_attn_dense(g, splits);
+}
 extern "C" long emu_wave_ops() { return emu::wave_ops; }
 """
 
@@ -242,6 +247,16 @@ def test_values_not_finite(emu, bad, masked, page):
     (1, 15, 15, 512, 32, 8, 1, False)])
 def test_masked_tiles_where_they_measured_faster(emu, batch, n_q, n, k, qh, kvh, splits, tiles):
     assert bool(emu.emu_masked(batch, n_q, n, k, qh, kvh, splits)) == tiles
+
+
+@pytest.mark.parametrize("batch,n_q,n,qh,kvh,splits,tiles", [
+    (4, 32, 600, 64, 8, 1, False), (3, 64, 300, 64, 8, 1, False), (1, 150, 600, 64, 8, 1, False),
+    (1, 64, 1000, 64, 8, 2, False), (4, 64, 600, 20, 4, 1, False), (1, 500, 600, 20, 4, 1, False),
+    (1, 1000, 1000, 20, 4, 3, True), (3, 500, 600, 64, 8, 8, True), (1, 500, 1000, 64, 8, 1, True),
+    (1, 500, 600, 8, 8, 1, True), (8, 16, 4096, 32, 8, 1, True), (1, 16, 32768, 32, 8, 8, True),
+    (1, 8192, 8192, 20, 4, 8, True), (1, 15, 65536, 32, 8, 9, False), (1, 64, 600, 32, 8, 2, False)])
+def test_dense_tiles_where_they_measured_faster(emu, batch, n_q, n, qh, kvh, splits, tiles):
+    assert bool(emu.emu_dense(batch, n_q, n, 1, qh, kvh, splits)) == tiles
 
 
 def test_mask_of_long_rows(emu):
