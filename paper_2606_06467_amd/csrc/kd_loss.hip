@@ -625,6 +625,14 @@ __global__ __launch_bounds__(256, 1) void kd_grad_kernel(KdLossArgs a) {
 #pragma unroll
             for (int e = 0; e < 16; e += 2) pieces2(e, hi, lse, c, p, lim, sk, sb, pl);
 #pragma unroll
+            for (int i = 0; i < 8; ++i) {  // an infinite Q - P (of an infinite target) is its first piece alone
+                const uint32_t f = pl[0][i];
+                const uint32_t keep = ((f & 0x7fffu) == 0x7f80u ? 0u : 0x0000ffffu) |
+                                      ((f & 0x7fff0000u) == 0x7f800000u ? 0u : 0xffff0000u);
+                pl[1][i] &= keep;
+                pl[2][i] &= keep;
+            }
+#pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int d = 0; d < 8; ++d) {

@@ -183,3 +183,19 @@ def test_target_not_a_number(emu):
     assert loss == without
     assert np.isnan(dq[0, 1]).all() and np.isfinite(dq[0, [0, 2]]).all()
     assert np.isnan(dk[0, 70]).all() and np.isfinite(np.delete(dk[0], 70, axis=0)).all()
+
+
+def test_target_infinite(emu):
+    """An infinite target makes the gradients of its row and key infinite, as one product
+    of each value with Q - P does."""
+    w = inputs.small_workload(batch=1, lens=(100,), n_q=40, n_layers=1, q_heads=8, kv_heads=8, wid=108)
+    x, abar = _inputs(w)
+    for bad in (np.inf, -np.inf):
+        abar[0, 33, 70] = bad
+        _, dq, dk = _run(emu, w, x, abar)
+        for got, ref in zip((dq, dk), _float_model(w, x, abar)):
+            assert np.array_equal(np.isnan(got), np.isnan(ref))
+            hit = np.isinf(ref)
+            assert hit.sum() >= 250 and np.array_equal(got[hit], ref[hit])
+            ok = np.isfinite(ref)
+            assert np.abs(got[ok] - ref[ok]).max() <= 1e-5 * np.abs(ref[ok]).max() + 1e-7
