@@ -695,8 +695,7 @@ __global__ __launch_bounds__(256) void kd_finish_rows_kernel(KdLossArgs a) {
     const int n = valid_keys(a.seq_lens, a.q_pos, a.causal, row / a.n_q, row, a.max_len);
     const int used = div_up(n, a.span);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    // the row term by tiles, so that a long range is no chain of its length
-    float kl = 0.0f, total = 0.0f;
+    float kl = 0.0f;
     for (int k = 0; k < used; ++k) {
         const float4 v = *reinterpret_cast<const float4 *>(a.part + ((size_t)k * a.rows + row) * kIdxDim + c);
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;

@@ -225,8 +225,9 @@ __global__ __launch_bounds__(256, 2) void project_gemm_kernel(ProjArgs a) {
         // step (the last step stores an old piece that is not read).  8192 rows x 2560
         // features x 2560: 127.6 us with padded rows and the compiler's order, 124.0
         // swizzled, 117.4 in this order; 32-wide steps (three workgroups per CU) 139.6.
-        // What bounds it now: 640 tiles on 512 resident workgroups, and the step's
-        // own chain of barrier, operand reads and products at two waves per SIMD.
+        // What bounds it now: 1280 tiles on 512 resident workgroups are 2.5 rounds, and
+        // the step's own chain of barrier, operand reads and products at two waves per
+        // SIMD.
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
             const int ks = p >> 3;
